@@ -111,60 +111,26 @@ pic::AttnShape shape_of(const pic_model* m, int32_t batch, int32_t cache_cap, fl
 pic_status check_attn_model(const pic_model* m) { return check_model(m); }
 
 // bf16 caches run on the matrix-core kernels (prefill in every mode and decode, head_dim 128 or
-// 64); float32 caches on the row-wise kernel.
+// 64); float32 caches on the float32 kernel.
 bool mfma_prefill(const pic_model* m) { return m->dtype == PIC_BF16; }
 bool mfma_decode(const pic_model* m) { return m->dtype == PIC_BF16; }
 
-// Row-wise attention of n_q query rows per request at the positions `pos` gives them.
-// Options for bf16 rows: q_table (fused RoPE of the query), and a paged key source.
-struct RowOpts {
-  const void* q_table = nullptr;
-  int64_t table_stride = 0;
-  int32_t max_abs_delta = 0;
-  const void* pool_k = nullptr;
-  const void* pool_v = nullptr;
-  int64_t pool_tokens = 0;
-  const int32_t* smap = nullptr;
-  const int32_t* dmap = nullptr;
-  int32_t map_cap = 0;
-  const int32_t* ctx_len = nullptr;
-  int32_t max_ctx = 0;
-  const void* k_table = nullptr;
-};
-template <typename T>
-hipError_t launch_rows_as(const pic_model* m, const pic::AttnShape& s, const void* q, const void* ck,
-                          const void* cv, const pic::RowPos& pos, int32_t n_q, void* out, const RowOpts& o,
-                          hipStream_t st) {
-  pic::RowArgs<T> a;
+// Attention over a float32 cache: n_q query rows per request at the positions `pos` gives them.
+// k_new / v_new: the call's own tokens, to be stored too (NULL: already in the cache).
+pic_status launch_f32(const pic::AttnShape& s, const void* q, const void* k_new, const void* v_new, void* ck, void* cv,
+                      const pic::RowPos& pos, int32_t n_q, void* out, hipStream_t st, const char* what) {
+  pic::F32AttnArgs a;
   a.s = s;
-  a.q = static_cast<const T*>(q);
-  a.cache_k = static_cast<const T*>(ck);
-  a.cache_v = static_cast<const T*>(cv);
+  a.q = static_cast<const float*>(q);
+  a.k_new = static_cast<const float*>(k_new);
+  a.v_new = static_cast<const float*>(v_new);
+  a.cache_k = static_cast<float*>(ck);
+  a.cache_v = static_cast<float*>(cv);
   a.pos = pos;
   a.n_q = n_q;
-  a.out = static_cast<T*>(out);
-  a.q_table = static_cast<const float2*>(o.q_table);
-  a.k_table = static_cast<const float2*>(o.k_table);
-  a.table_stride = o.table_stride;
-  a.max_abs_delta = o.max_abs_delta;
-  a.interleaved = m->rope_pairing == PIC_ROPE_INTERLEAVED;
-  a.pool_k = static_cast<const T*>(o.pool_k);
-  a.pool_v = static_cast<const T*>(o.pool_v);
-  a.pool_tokens = o.pool_tokens;
-  a.smap = o.smap;
-  a.dmap = o.dmap;
-  a.map_cap = o.map_cap;
-  a.ctx_len = o.ctx_len;
-  a.max_ctx = o.max_ctx;
+  a.out = static_cast<float*>(out);
   a.stream = st;
-  return pic::launch_attn_rows(a);
-}
-pic_status launch_rows(const pic_model* m, const pic::AttnShape& s, const void* q, const void* ck, const void* cv,
-                       const pic::RowPos& pos, int32_t n_q, void* out, hipStream_t st, const char* what,
-                       const RowOpts& o = RowOpts()) {
-  return hip_status(m->dtype == PIC_F32 ? launch_rows_as<float>(m, s, q, ck, cv, pos, n_q, out, o, st)
-                                        : launch_rows_as<pic::bf16_t>(m, s, q, ck, cv, pos, n_q, out, o, st),
-                    what);
+  return hip_status(pic::launch_attn_f32(a), what);
 }
 
 }  // namespace
@@ -557,17 +523,13 @@ PIC_API pic_status pic_suffix_prefill_attn(const pic_model* model, const void* q
     return fail(PIC_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", need, ws_bytes);
   const hipStream_t st = (hipStream_t)stream;
   const pic::AttnShape s = shape_of(model, batch, cache_cap, scale);
-  // a4: suffix K/V into slots [ctx, ctx + n_suffix) (App. C.1: inline KVs interleaved); the
-  // bf16 matrix-core kernel does this itself
+  // a4: both kernels store the suffix K/V into slots [ctx, ctx + n_suffix) (App. C.1: inline
+  // KVs interleaved)
   if (!mfma_prefill(model)) {
     pic::RowPos pos;
     pos.base = ctx_len;
     pos.max_base = max_ctx;
-    PIC_CHECK(hip_status(pic::launch_append(model->dtype, model->head_dim, model->n_layers,
-                                            model->n_kv_heads, k_suf, v_suf, cache_k, cache_v,
-                                            batch, cache_cap, pos, n_suffix, st),
-                         "suffix append launch"));
-    return launch_rows(model, s, q, cache_k, cache_v, pos, n_suffix, out, st, "prefill attention launch");
+    return launch_f32(s, q, k_suf, v_suf, cache_k, cache_v, pos, n_suffix, out, st, "prefill attention launch");
   }
   return hip_status(pic::launch_prefill_bf16(s, static_cast<const pic::bf16_t*>(q),
                                              static_cast<const pic::bf16_t*>(k_suf),
@@ -803,7 +765,7 @@ PIC_API pic_status pic_frontier_prefill_attn(const pic_model* model, const void*
                                           batch, cache_cap, rp, n_inline, st),
                        "inline append launch"));
   if (!mfma_prefill(model))
-    return launch_rows(model, s, q, cache_k, cache_v, rp, n_inline, out, st, "frontier attention launch");
+    return launch_f32(s, q, nullptr, nullptr, cache_k, cache_v, rp, n_inline, out, st, "frontier attention launch");
   return hip_status(pic::launch_prefill_bf16_table(s, static_cast<const pic::bf16_t*>(q),
                                                    static_cast<const pic::bf16_t*>(cache_k),
                                                    static_cast<const pic::bf16_t*>(cache_v), rp,
@@ -871,31 +833,12 @@ pic_status decode_impl(const pic_model* model, const void* q, const void* k_new,
   }
   const hipStream_t st = (hipStream_t)stream;
   const pic::AttnShape s = shape_of(model, batch, cache_cap, scale);
-  if (!mfma_decode(model)) {   // float32: row-wise kernel, no splits
+  if (!mfma_decode(model)) {   // float32 (never with a table): no splits over workgroups
     pic::RowPos pos;
     pos.base = base_len;
     pos.max_base = max_base_len;
     pos.offset = step;
-    const int64_t stride = n_tables(model) > 1 ? (int64_t)(max_abs_delta + 1) * (model->head_dim / 2) : 0;
-    if (table)
-      PIC_CHECK(hip_status(pic::launch_append_rope(model->head_dim, model->rope_pairing == PIC_ROPE_INTERLEAVED,
-                                                   model->n_layers, model->n_kv_heads,
-                                                   static_cast<const pic::bf16_t*>(k_new),
-                                                   static_cast<const pic::bf16_t*>(v_new),
-                                                   static_cast<pic::bf16_t*>(cache_k),
-                                                   static_cast<pic::bf16_t*>(cache_v), batch, cache_cap, pos, 1,
-                                                   static_cast<const float2*>(table), stride, max_abs_delta, st),
-                           "decode append launch"));
-    else
-      PIC_CHECK(hip_status(pic::launch_append(model->dtype, model->head_dim, model->n_layers,
-                                              model->n_kv_heads, k_new, v_new, cache_k, cache_v,
-                                              batch, cache_cap, pos, 1, st),
-                           "decode append launch"));
-    RowOpts o;
-    o.q_table = table;
-    o.table_stride = stride;
-    o.max_abs_delta = max_abs_delta;
-    return launch_rows(model, s, q, cache_k, cache_v, pos, 1, out, st, "decode attention launch", o);
+    return launch_f32(s, q, k_new, v_new, cache_k, cache_v, pos, 1, out, st, "decode attention launch");
   }
   if (n_splits == 0) n_splits = pic::decode_bf16_auto_splits(s, (int32_t)max_len);
   if ((int64_t)n_splits * batch * model->n_kv_heads * ((model->n_q_heads / model->n_kv_heads + 15) / 16) > INT32_MAX)

@@ -161,9 +161,9 @@ hipError_t launch_append(pic_dtype dt, int head_dim, int n_layers, int n_kv_head
   return hipSuccess;
 }
 
-namespace {
-template <typename T>
-hipError_t rows_walk(const RowArgs<T>& a) {
+// float32 attention: every slot a used row sees is read from the cache, the call's own tokens
+// (k_new given) from k_new / v_new, and those are stored into their slots
+hipError_t launch_attn_f32(const F32AttnArgs& a) {
   const AttnShape& s = a.s;
   const int HD = s.head_dim, Hq = s.n_q_heads, Hkv = s.n_kv_heads, n_q = a.n_q;
   const int64_t rows = (int64_t)s.batch * n_q * Hq;
@@ -175,20 +175,17 @@ hipError_t rows_walk(const RowArgs<T>& a) {
       const int g = h / (Hq / Hkv);
       const int64_t qpos = a.pos(b, i);
       if (qpos < 0) continue;
-      int64_t n_vis = qpos + 1;
-      if (n_vis > s.cache_cap) n_vis = s.cache_cap;
       const int64_t qrow = (int64_t)l * s.batch * n_q * Hq + row;
       emu::rd(a.q, qrow, HD);
-      if (a.q_table) rd_row(a.q_table + l * a.table_stride, std::min<int64_t>(qpos, a.max_abs_delta), (int64_t)HD / 2 * 8);
       const int64_t kv0 = (((int64_t)l * s.batch + b) * Hkv + g) * s.cache_cap;
-      const int32_t ctx = a.pool_k ? clamp_len(a.ctx_len[b], a.max_ctx) : 0;
-      for (int64_t j = 0; j < n_vis; ++j) {
-        if (a.pool_k && j < ctx) {
-          const int32_t src = clamp_pool_token(a.smap[(int64_t)b * a.map_cap + j], a.pool_tokens);
-          const int32_t dl = clamp_delta(a.dmap[(int64_t)b * a.map_cap + j], a.max_abs_delta);
-          rd_row(a.k_table + l * a.table_stride, iabs(dl), (int64_t)HD / 2 * 8);
-          emu::rd(a.pool_k, ((int64_t)l * Hkv + g) * a.pool_tokens + src, HD);
-          emu::rd(a.pool_v, ((int64_t)l * Hkv + g) * a.pool_tokens + src, HD);
+      const int64_t fresh = a.k_new ? a.pos(b, 0) : INT64_MAX;
+      for (int64_t j = 0; j <= qpos; ++j) {
+        if (j >= fresh) {
+          const int64_t nrow = (((int64_t)l * s.batch + b) * n_q + (j - fresh)) * Hkv + g;
+          emu::rd(a.k_new, nrow, HD);
+          emu::rd(a.v_new, nrow, HD);
+          emu::wr(a.cache_k, kv0 + j, HD);
+          emu::wr(a.cache_v, kv0 + j, HD);
         } else {
           emu::rd(a.cache_k, kv0 + j, HD);
           emu::rd(a.cache_v, kv0 + j, HD);
@@ -197,29 +194,6 @@ hipError_t rows_walk(const RowArgs<T>& a) {
       emu::wr(a.out, qrow, HD);
     }
   return hipSuccess;
-}
-}  // namespace
-
-hipError_t launch_attn_rows(const RowArgs<float>& a) { return rows_walk(a); }
-hipError_t launch_attn_rows(const RowArgs<bf16_t>& a) { return rows_walk(a); }
-
-hipError_t launch_append_rope(int head_dim, bool, int n_layers, int n_kv_heads, const bf16_t* k_new,
-                              const bf16_t* v_new, bf16_t* cache_k, bf16_t* cache_v, int32_t batch,
-                              int32_t cache_cap, const RowPos& pos, int32_t n_new, const float2* table,
-                              int64_t table_stride, int32_t max_abs_delta, hipStream_t stream) {
-  const int64_t n_rows = (int64_t)n_layers * batch * n_new * n_kv_heads;
-  if (n_rows == 0) return hipSuccess;
-  for (int64_t row = 0; row < n_rows; ++row) {   // the table row of each placed key
-    const int64_t r1 = row / n_kv_heads;
-    const int i = (int)(r1 % n_new);
-    const int64_t lb = r1 / n_new;
-    const int b = (int)(lb % batch), l = (int)(lb / batch);
-    const int64_t slot = pos(b, i);
-    if (slot < 0 || slot >= cache_cap) continue;
-    rd_row(table + l * table_stride, std::min<int64_t>(slot, max_abs_delta), (int64_t)head_dim / 2 * 8);
-  }
-  return launch_append(PIC_BF16, head_dim, n_layers, n_kv_heads, k_new, v_new, cache_k, cache_v, batch, cache_cap,
-                       pos, n_new, stream);
 }
 
 // ---- bf16 prefill: one walk serves every mode of prefill_bf16_kernel ----
