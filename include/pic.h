@@ -352,14 +352,16 @@ pic_status pic_frontier_prefill_attn(const pic_model* model, const void* q, cons
 /* ---- 4. decode (App. C.1: ordinary autoregressive decoding over the completed cache) ----
    For request b the new token sits at slot p = base_len[b] + step: k_new/v_new are written
    there, then its query attends over slots [0, p].  Split-K over the context: n_splits
-   chunks per (request, kv head) (0 picks a value), merged by log-sum-exp; a kv head with
+   chunks per (request, kv head) on average (0 picks a value; with 8 or more and up to 64 requests
+   longer contexts get more of them), merged by log-sum-exp; a kv head with
    more than 16 query heads is served in groups of 16.  The float32 kernel ignores
    n_splits.
      base_len [device, batch]  valid slots before the first decode step; clamped to
                                [0, max_base_len]; max_base_len + step + 1 <= cache_cap
      workspace                 pic_decode_workspace_bytes(...) bytes for the same batch,
                                max_base_len + step + 1 and n_splits; 0 bytes (NULL allowed)
-                               when the split count is 1 */
+                               when the split count is 1.  With n_splits 0, a call of 256 or more
+                               (request, kv head, layer) triples that brings less runs unsplit. */
 size_t pic_decode_workspace_bytes(const pic_model* model, int32_t batch, int32_t max_len,
                                   int32_t n_splits);
 pic_status pic_decode_attn(const pic_model* model, const void* q, const void* k_new,

@@ -20,7 +20,9 @@
 //  * the new token's K/V are read straight from k_new/v_new by the wave whose range holds slot p,
 //    and written into the cache by that workgroup (no separate append launch);
 //  * the 4 waves merge by log-sum-exp in LDS; a context split over several workgroups (only when
-//    (request, kv head) pairs alone do not fill the GPU) leaves fp32 partials for a combine pass;
+//    (request, kv head) pairs alone do not fill the GPU) leaves fp32 partials for a combine pass.
+//    The workgroups of a split launch are dealt to the requests by length (see SplitDeal), so
+//    a batch of uneven contexts keeps every compute unit at the same amount of keys;
 //  * rope variant: q and k_new arrive unrotated and are turned to position p (the delta-angle
 //    table's row p) in registers -- the query once, the new key in the tile that holds it and
 //    where it is stored -- with the float32 arithmetic of the re-rotation kernel.
@@ -54,6 +56,7 @@ struct Dims {
   static constexpr int kBlocks = HD / 16;                   // 16-dim output blocks
   static constexpr int kRowsPerMove = 64 / kChunks;         // rows one 1 KB V move fills
 };
+static_assert(kDecodeUnit == kWaves * kTile, "a unit is one tile per wave");
 static_assert(kWaves == kDecodeWaves && kMinWaveKeys == kDecodeMinWaveKeys, "host split planner tiling");
 constexpr int kNonTemporal = 2;                    // cache-policy bits of a streaming load
 
@@ -80,8 +83,8 @@ struct DecodeArgs {
   bf16_t* cache_v;
   const int32_t* base_len;
   bf16_t* out;            // [L][B][Hq][D]
-  float* ws_o;            // [L][B][Hq][S][D]   (n_splits > 1)
-  float* ws_ml;           // [L][B][Hq][S][2]
+  float* ws_o;            // [L][slots][D]   (n_splits > 1; slots = B Hq n_splits, see SplitDeal)
+  float* ws_ml;           // [L][slots][2]
   int32_t batch, cache_cap, n_q_heads, n_kv_heads, max_base, step, n_splits, chunk;
   int32_t head_groups;    // groups of up to 16 query heads per kv head (ceil(n_rep / 16))
   float scale_log2;
@@ -89,6 +92,61 @@ struct DecodeArgs {
   int64_t table_stride;
   int32_t max_abs_delta;
 };
+
+// How the key ranges of a split launch are dealt to the requests (pic_bounds.h): worked out by
+// every wave from the context lengths, request b in lane b.  Request b's partials are slots
+// [Hq first, Hq (first + n)), query head by query head.  Contexts of one length take a short way
+// to the same ranges (the long one costs about 0.5 us, paid in the kernel and its combine).
+struct SplitDeal {
+  int32_t chunk;   // keys per range, a multiple of 128
+  int32_t n;       // ranges of every request; -1: lane b holds those of request b in mine
+  int32_t mine;
+  int32_t base;    // dealt: lane b holds the context length of request b
+};
+struct SplitPlace {
+  int32_t n, first;   // ranges of the request; those of the requests before it
+};
+// ceil(u / c) for 0 <= u < 2^24, 1 <= c, inv ~ 1 / c: a float32 quotient, off by one at most, put right
+__device__ __forceinline__ int32_t ceil_div24(int32_t u, int32_t c, float inv) {
+  int32_t q = (int32_t)((float)u * inv);
+  const int32_t r = u - q * c;
+  return q + (r > 0 ? 1 : 0) + (r > c ? 1 : 0) - (r <= -c ? 1 : 0);
+}
+__device__ __forceinline__ SplitDeal deal_splits(const int32_t* base_len, int32_t batch, int32_t max_base, int32_t step,
+                                                 int32_t cache_cap, int32_t n_splits, int32_t chunk) {
+  if (!decode_dealt(n_splits, batch, max_base + step + 1)) return {chunk, n_splits, 0, 0};
+  const int lane = threadIdx.x & 63;
+  int32_t u = 0, base = 0;
+  if (lane < batch) {
+    base = clamp_len(base_len[lane], max_base);
+    u = decode_units(min(base + step + 1, cache_cap));
+  }
+  const int32_t u0 = __builtin_amdgcn_readfirstlane(u);
+  if (__ballot(lane < batch && u != u0) == 0) {
+    const int32_t s = min(n_splits, u0), cu = __builtin_amdgcn_readfirstlane(ceil_div24(u0, s, __builtin_amdgcn_rcpf((float)s)));
+    return {cu * kDecodeUnit, __builtin_amdgcn_readfirstlane(ceil_div24(u0, cu, __builtin_amdgcn_rcpf((float)cu))), 0, base};
+  }
+  int32_t total = 0, longest = 0;
+  for (int b = 0; b < batch; ++b) {
+    const int32_t ub = __builtin_amdgcn_readlane(u, b);
+    total += ub;
+    longest = max(longest, ub);
+  }
+  const RangeCandidates rc = decode_range_candidates(total, longest, n_splits, batch);
+  const int32_t c = rc.at(lane);   // lane i weighs candidate i
+  const float inv = __builtin_amdgcn_rcpf((float)c);
+  int32_t sum = 0;
+  for (int b = 0; b < batch; ++b) sum += ceil_div24(__builtin_amdgcn_readlane(u, b), c, inv);
+  const uint64_t fits = __ballot(sum <= n_splits * batch);   // (lane 63: always)
+  const int32_t cu = __builtin_amdgcn_readlane(c, __ffsll((unsigned long long)fits) - 1);
+  return {cu * kDecodeUnit, -1, ceil_div24(u, cu, __builtin_amdgcn_rcpf((float)cu)), base};
+}
+__device__ __forceinline__ SplitPlace place_of(const SplitDeal& d, int b) {   // b uniform
+  if (d.n >= 0) return {d.n, b * d.n};
+  SplitPlace p = {__builtin_amdgcn_readlane(d.mine, b), 0};
+  for (int i = 0; i < b; ++i) p.first += __builtin_amdgcn_readlane(d.mine, i);
+  return p;
+}
 
 // (x, y) turned by (c, s) in the float32 form of the re-rotation kernel.
 __device__ __forceinline__ void rot_pair(float& x, float& y, float c, float s) {
@@ -155,21 +213,49 @@ decode_bf16_kernel(DecodeArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hgrp = blockIdx.x % a.head_groups;           // query heads 16 hgrp .. of kv head g
-  const int split = (blockIdx.x / a.head_groups) % a.n_splits;
-  const int bg = blockIdx.x / (a.head_groups * a.n_splits);
-  const int b = bg / a.n_kv_heads, g = bg % a.n_kv_heads;
+  const int at = blockIdx.x / a.head_groups;             // [request][kv head][range]
+  const bool dealt = decode_dealt(a.n_splits, a.batch, a.max_base + a.step + 1);
+  int b, g, split, chunk = a.chunk;
+  int32_t base;
+  SplitPlace place;
+  if (!dealt) {
+    split = at % a.n_splits;
+    const int bg = at / a.n_splits;
+    b = bg / a.n_kv_heads;
+    g = bg % a.n_kv_heads;
+    place = {a.n_splits, b * a.n_splits};
+    base = clamp_len(a.base_len[b], a.max_base);
+  } else {
+    const SplitDeal deal = deal_splits(a.base_len, a.batch, a.max_base, a.step, a.cache_cap, a.n_splits, a.chunk);
+    chunk = deal.chunk;
+    if (deal.n >= 0) {
+      b = at / (deal.n * a.n_kv_heads);
+      place = place_of(deal, b);
+    } else {
+      place = {0, 0};
+      for (b = 0; b < a.batch; ++b) {
+        place.n = __builtin_amdgcn_readlane(deal.mine, b);
+        if (at < (place.first + place.n) * a.n_kv_heads) break;
+        place.first += place.n;
+      }
+    }
+    if (b >= a.batch) return;   // (uniform) more workgroups than ranges
+    const int in_b = at - place.first * a.n_kv_heads;
+    g = in_b / place.n;
+    split = in_b - g * place.n;
+    base = __builtin_amdgcn_readlane(deal.base, b);
+  }
   const int l = blockIdx.y;
   const int n_rep = a.n_q_heads / a.n_kv_heads;
   const int rep0 = 16 * hgrp;                             // first query head of this group
   const int n_here = min(16, n_rep - rep0);               // query heads of this group
 
-  const int32_t base = clamp_len(a.base_len[b], a.max_base);
   const int p = base + a.step;                       // the new token's slot
   int n_vis = p + 1;
   if (n_vis > a.cache_cap) n_vis = a.cache_cap;
-  const int wc0 = min(split * a.chunk, n_vis);
-  const int wc1 = min(wc0 + a.chunk, n_vis);
-  const int sub = a.chunk / kWaves;                  // multiple of kTile
+  const int wc0 = (int)min((int64_t)split * chunk, (int64_t)n_vis);
+  const int wc1 = (int)min((int64_t)wc0 + chunk, (int64_t)n_vis);
+  const int sub = chunk / kWaves;                  // multiple of kTile
   const int c0 = min(wc0 + wave * sub, wc1);
   const int c1 = min(c0 + sub, wc1);
 
@@ -389,7 +475,7 @@ decode_bf16_kernel(DecodeArgs a) {
       o[4] += wt * x1.x; o[5] += wt * x1.y; o[6] += wt * x1.z; o[7] += wt * x1.w;
     }
     const int64_t row = ((int64_t)l * a.batch + b) * a.n_q_heads + g * n_rep + rep0 + mn;
-    if (a.n_splits == 1) {
+    if (place.n == 1) {
       const float inv = 1.f / den;
       uint4 v;
       v.x = pack_bf16x2(o[0] * inv, o[1] * inv);
@@ -398,7 +484,8 @@ decode_bf16_kernel(DecodeArgs a) {
       v.w = pack_bf16x2(o[6] * inv, o[7] * inv);
       *reinterpret_cast<uint4*>(a.out + row * kHD + md) = v;
     } else {
-      const int64_t slot = row * a.n_splits + split;
+      const int64_t slot = ((int64_t)l * a.batch * a.n_splits + place.first) * a.n_q_heads +
+                           (int64_t)(g * n_rep + rep0 + mn) * place.n + split;
       float* wo = a.ws_o + slot * kHD + md;
       *reinterpret_cast<float4*>(wo) = make_float4(o[0], o[1], o[2], o[3]);
       *reinterpret_cast<float4*>(wo + 4) = make_float4(o[4], o[5], o[6], o[7]);
@@ -407,47 +494,68 @@ decode_bf16_kernel(DecodeArgs a) {
   }
 }
 
-// grid (B * Hq, L), HD / 2 threads (two head dims each): merge the splits of one query head by
-// log-sum-exp.  The loads of kCombineBatch splits are issued together before any is used (one
-// pass for the maximum, one for the weighted sums); a split that saw no key (maximum -inf) adds
-// nothing.
-constexpr int kCombineBatch = 8;
+// grid (B * Hq, L), 256 threads: merge the ranges of one query head by log-sum-exp.  HD / 4 lanes
+// hold 4 head dims each of one range, 1024 / HD ranges side by side, and every range's loads are
+// issued before any is used; the range groups then merge in LDS.  (One wave walking the ranges
+// took 4.9 us for 8 or 32 of them: a memory round trip per 8, once for the maxima and once for
+// the sums.)  A range that saw no key (maximum -inf) adds nothing.
 template <int HD>
-__global__ void __launch_bounds__(64) decode_combine_kernel(const float* __restrict__ ws_o,
-                                                            const float* __restrict__ ws_ml,
-                                                            int32_t n_splits, int64_t rows_per_layer,
-                                                            bf16_t* __restrict__ out) {
-  const int64_t row = (int64_t)blockIdx.y * rows_per_layer + blockIdx.x;
-  const float* ml = ws_ml + row * n_splits * 2;
-  float M = -INFINITY;
-  for (int s0 = 0; s0 < n_splits; s0 += kCombineBatch) {
-    float mv[kCombineBatch];
+__global__ void __launch_bounds__(256) decode_combine_kernel(const float* __restrict__ ws_o,
+                                                             const float* __restrict__ ws_ml,
+                                                             const int32_t* __restrict__ base_len, int32_t batch,
+                                                             int32_t n_q_heads, int32_t max_base, int32_t step,
+                                                             int32_t cache_cap, int32_t n_splits, int32_t chunk,
+                                                             bf16_t* __restrict__ out) {
+  constexpr int kLanes = HD / 4, kGroups = 256 / kLanes, kBatch = 4;
+  __shared__ float m_s[kGroups], l_s[kGroups];
+  __shared__ __attribute__((aligned(16))) float o_s[kGroups * HD];
+  const int b = blockIdx.x / n_q_heads, h = blockIdx.x - b * n_q_heads, l = blockIdx.y;
+  const SplitPlace place = place_of(deal_splits(base_len, batch, max_base, step, cache_cap, n_splits, chunk), b);
+  if (place.n == 1) return;   // (uniform) a whole request: its output is stored
+  const int64_t slot0 = ((int64_t)l * batch * n_splits + place.first) * n_q_heads + (int64_t)h * place.n;
+  const int grp = threadIdx.x / kLanes, d = 4 * (threadIdx.x % kLanes);
+  float M = -INFINITY, den = 0.f;
+  f32x4_t o = {};
+  for (int s0 = grp; s0 < place.n; s0 += kBatch * kGroups) {
+    float2 ml[kBatch];
+    f32x4_t x[kBatch];
 #pragma unroll
-    for (int u = 0; u < kCombineBatch; ++u) mv[u] = s0 + u < n_splits ? ml[2 * (s0 + u)] : -INFINITY;
-#pragma unroll
-    for (int u = 0; u < kCombineBatch; ++u) M = fmaxf(M, mv[u]);
-  }
-  float den = 0.f, o0 = 0.f, o1 = 0.f;
-  const int d = 2 * threadIdx.x;
-  for (int s0 = 0; s0 < n_splits; s0 += kCombineBatch) {
-    float2 mlv[kCombineBatch], ov[kCombineBatch];
-#pragma unroll
-    for (int u = 0; u < kCombineBatch; ++u) {
-      const int s = s0 + u;
-      mlv[u] = s < n_splits ? *reinterpret_cast<const float2*>(ml + 2 * s) : make_float2(-INFINITY, 0.f);
-      ov[u] = s < n_splits ? *reinterpret_cast<const float2*>(ws_o + (row * n_splits + s) * HD + d)
-                           : make_float2(0.f, 0.f);
+    for (int u = 0; u < kBatch; ++u) {
+      const int s = s0 + u * kGroups;
+      ml[u] = s < place.n ? *reinterpret_cast<const float2*>(ws_ml + 2 * (slot0 + s)) : make_float2(-INFINITY, 0.f);
+      x[u] = s < place.n ? *reinterpret_cast<const f32x4_t*>(ws_o + (slot0 + s) * HD + d) : f32x4_t{};
     }
 #pragma unroll
-    for (int u = 0; u < kCombineBatch; ++u) {
-      if (mlv[u].x == -INFINITY) continue;
-      const float w = __builtin_amdgcn_exp2f(mlv[u].x - M);
-      den += w * mlv[u].y;
-      o0 += w * ov[u].x;
-      o1 += w * ov[u].y;
+    for (int u = 0; u < kBatch; ++u) {
+      if (ml[u].x == -INFINITY) continue;
+      const float m_new = fmaxf(M, ml[u].x);
+      const float keep = __builtin_amdgcn_exp2f(M - m_new), w = __builtin_amdgcn_exp2f(ml[u].x - m_new);
+      M = m_new;
+      den = den * keep + w * ml[u].y;
+      o = o * keep + w * x[u];
     }
   }
-  const float inv = 1.f / den;
+  *reinterpret_cast<f32x4_t*>(o_s + grp * HD + d) = o;
+  if (d == 0) {
+    m_s[grp] = M;
+    l_s[grp] = den;
+  }
+  __syncthreads();
+  if (threadIdx.x >= HD / 2) return;
+  float m_all = -INFINITY;
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) m_all = fmaxf(m_all, m_s[g]);
+  float l_all = 0.f, o0 = 0.f, o1 = 0.f;
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) {
+    if (m_s[g] == -INFINITY) continue;
+    const float w = __builtin_amdgcn_exp2f(m_s[g] - m_all);
+    l_all += w * l_s[g];
+    o0 += w * o_s[g * HD + 2 * threadIdx.x];
+    o1 += w * o_s[g * HD + 2 * threadIdx.x + 1];
+  }
+  const float inv = 1.f / l_all;
+  const int64_t row = ((int64_t)l * batch + b) * n_q_heads + h;
   reinterpret_cast<uint32_t*>(out + row * HD)[threadIdx.x] = pack_bf16x2(o0 * inv, o1 * inv);
 }
 
@@ -462,8 +570,9 @@ hipError_t launch_decode_hd(const DecodeArgs& a, dim3 grid, bool rope, bool inte
     hipLaunchKernelGGL((decode_bf16_kernel<HD, true, false>), grid, dim3(256), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || n_splits == 1) return e;
-  hipLaunchKernelGGL(decode_combine_kernel<HD>, dim3(s.batch * s.n_q_heads, s.n_layers), dim3(HD / 2), 0,
-                     stream, a.ws_o, a.ws_ml, n_splits, (int64_t)s.batch * s.n_q_heads, a.out);
+  hipLaunchKernelGGL(decode_combine_kernel<HD>, dim3(s.batch * s.n_q_heads, s.n_layers), dim3(256), 0, stream,
+                     a.ws_o, a.ws_ml, a.base_len, s.batch, s.n_q_heads, a.max_base, a.step, a.cache_cap, n_splits,
+                     a.chunk, a.out);
   return hipGetLastError();
 }
 
@@ -518,8 +627,8 @@ hipError_t launch_decode_bf16(const AttnShape& s, const bf16_t* q, const bf16_t*
   a.max_base = max_base;
   a.step = step;
   a.n_splits = n_splits;
-  const int32_t chunk = (max_len + n_splits - 1) / n_splits;
-  a.chunk = (chunk + kWaves * kTile - 1) / (kWaves * kTile) * (kWaves * kTile);
+  const int32_t chunk = ceil_div(max_len, n_splits);
+  a.chunk = (int32_t)min((int64_t)decode_units(chunk) * kDecodeUnit, (int64_t)INT32_MAX / kDecodeUnit * kDecodeUnit);
   a.scale_log2 = s.scale_log2;
   a.table = rope_table;
   a.table_stride = table_stride;

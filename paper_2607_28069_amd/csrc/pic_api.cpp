@@ -840,7 +840,12 @@ pic_status decode_impl(const pic_model* model, const void* q, const void* k_new,
     pos.offset = step;
     return launch_f32(s, q, k_new, v_new, cache_k, cache_v, pos, 1, out, st, "decode attention launch");
   }
-  if (n_splits == 0) n_splits = pic::decode_bf16_auto_splits(s, (int32_t)max_len);
+  if (n_splits == 0) {
+    n_splits = pic::decode_bf16_auto_splits(s, (int32_t)max_len);
+    const size_t held = use_scratch ? pic::decode_scratch_bytes() : (workspace ? ws_bytes : 0);
+    if (pic::decode_bf16_workspace(s, (int32_t)max_len, n_splits) > held && pic::decode_bf16_may_run_whole(s))
+      n_splits = 1;
+  }
   if ((int64_t)n_splits * batch * model->n_kv_heads * ((model->n_q_heads / model->n_kv_heads + 15) / 16) > INT32_MAX)
     return fail(PIC_ERR_UNSUPPORTED, "too many splits");
   if (n_splits > max_len) n_splits = (int32_t)max_len;

@@ -82,4 +82,39 @@ PIC_HD bool tile_run_ok(int32_t src, int32_t delta, int32_t s0, int32_t ctx, int
          delta <= max_abs_delta && s0 + PIC_BLOCK_TOKENS <= ctx;
 }
 
+// ---- Split decode: the key ranges of a batch of uneven contexts ----
+// A split launch has n_splits workgroups per (request, kv head).  They are dealt to the requests
+// by length: request b of u_b units (kDecodeUnit keys each, the last one partial) gets
+// ceil(u_b / c) ranges of c units, c the smallest size for which the batch's ranges fit
+// n_splits * batch.  Candidate i of 64 for c, from the mean up to the size at which the longest
+// request alone takes n_splits ranges (which always fits):
+constexpr int32_t kDecodeUnit = 128;        // keys; every range is a multiple
+constexpr int32_t kDecodeDealt = 64;        // most requests whose ranges are dealt by length
+// Dealing takes 0.9 us (in the kernel and in its combine) and rounds each request's last range up,
+// so it is for launches of many ranges of long contexts.  Equal ranges / dealt: 8 requests of 16K
+// to 33K keys in 8 ranges each 81 / 68 us, of 33K each 86.6 / 87.3; 4 of 5K to 10K in 8 29.1 /
+// 25.8, 4 of 4K 16.4 / 17.3; 16 of 5K to 10K in 2 87.5 / 91.7.
+PIC_HD bool decode_dealt(int32_t n_splits, int32_t batch, int32_t max_len) {
+  return n_splits >= 8 && batch >= 2 && batch <= kDecodeDealt && max_len >= 8192;
+}
+PIC_HD int32_t decode_units(int32_t n_keys) { return (int32_t)(((uint32_t)n_keys + kDecodeUnit - 1) / kDecodeUnit); }
+PIC_HD int32_t ceil_div(int32_t n, int32_t d) { return (int32_t)(((uint32_t)n + (uint32_t)d - 1) / (uint32_t)d); }
+struct RangeCandidates {
+  int32_t lo, step, top;
+  PIC_HD int32_t at(int32_t i) const {   // i < 64: the last one is top
+    const int32_t c = lo + step * i;
+    return c < top ? c : top;
+  }
+};
+// (at most 64 requests of at most 2^24 units: every sum fits 32 bits)
+PIC_HD RangeCandidates decode_range_candidates(int32_t units_total, int32_t units_longest, int32_t n_splits,
+                                               int32_t batch) {
+  const int32_t s = n_splits < units_longest ? n_splits : units_longest;
+  RangeCandidates r;
+  r.lo = ceil_div(units_total, s * batch);
+  r.top = ceil_div(units_longest, s);
+  r.step = ceil_div(r.top > r.lo ? r.top - r.lo : 1, kDecodeDealt - 1);
+  return r;
+}
+
 }  // namespace pic

@@ -174,6 +174,7 @@ hipError_t launch_prefill_bf16_paged(const AttnShape& s, bool interleaved, const
                                      void* workspace, size_t ws_bytes, hipStream_t stream);
 
 int32_t decode_bf16_auto_splits(const AttnShape& s, int32_t max_len);
+bool decode_bf16_may_run_whole(const AttnShape& s);
 // Workgroups per (request, kv head, split) of the decode: one per group of up to 16 query heads.
 inline int32_t decode_head_groups(const AttnShape& s) { return (s.n_q_heads / s.n_kv_heads + 15) / 16; }
 // The decode scratch array (split-K partials of the allocation-free entry point): its size,

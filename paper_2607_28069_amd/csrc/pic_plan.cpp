@@ -51,18 +51,34 @@ size_t prefill_bf16_workspace(const AttnShape& s, int32_t n_suffix, int32_t max_
 
 int32_t slot_map_tiles(int32_t map_cap) { return (int32_t)(((int64_t)map_cap + kPrefillKeys - 1) / kPrefillKeys); }
 
-// Decode workgroups per (request, kv head, group of 16 query heads): enough 4-wave workgroups
-// for one per compute unit
-// (256 per launch; measured faster than two per unit on split launches), each wave keeping at
-// least kDecodeMinWaveKeys keys.
+// Key ranges per (request, kv head, group of 16 query heads).  One workgroup alone on a compute
+// unit streams about 36 GB/s, so some 200 of the 256 reach the HBM's rate and what counts is that
+// no compute unit gets one workgroup more than the others:
+//  * up to 128 pairs, as many ranges as leave at most one workgroup per compute unit, each wave
+//    keeping at least kDecodeMinWaveKeys keys (a second one on a few units costs as much as on all:
+//    192 pairs of 10K keys took 150 us in 1 range and 168 us in 2, 160 pairs of 8K 104 and 117);
+//  * from 129 to 256, none;
+//  * beyond, none if the last round of 256 is nearly full or the ranges would be short, else 4
+//    (264 pairs of 8K keys: 241 us whole, 191 us in 4; 320: 235 and 197; 384: 264 and 253; but 480
+//    pairs of 2K keys 71 and 95).  Head_dim 64 keeps four workgroups on a compute unit, which
+//    evens that out by itself (384 pairs: 120 us whole, 137 us in 4).
 int32_t decode_bf16_auto_splits(const AttnShape& s, int32_t max_len) {
   const int64_t pairs = (int64_t)s.batch * s.n_kv_heads * s.n_layers * decode_head_groups(s);
-  int64_t splits = (256 + pairs - 1) / pairs;
+  if (pairs > 256) {
+    const int64_t rounds = (pairs + 255) / 256;
+    return s.head_dim == 128 && max_len >= 4096 && rounds * 256 * 10 >= pairs * 13 ? 4 : 1;
+  }
+  int64_t splits = pairs > 0 ? 256 / pairs : 1;
   const int64_t per_split = (int64_t)kDecodeWaves * kDecodeMinWaveKeys;
   const int64_t max_splits = (max_len + per_split - 1) / per_split;
   if (splits > max_splits) splits = max_splits;
   if (splits < 1) splits = 1;
   return (int32_t)splits;
+}
+
+// Launches that fill the GPU unsplit: with no split count asked for they run without a workspace.
+bool decode_bf16_may_run_whole(const AttnShape& s) {
+  return (int64_t)s.batch * s.n_kv_heads * s.n_layers * decode_head_groups(s) >= 256;
 }
 
 size_t decode_bf16_workspace(const AttnShape& s, int32_t, int32_t n_splits) {

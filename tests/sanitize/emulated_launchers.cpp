@@ -6,9 +6,11 @@
 // The test driver hands the C ABI host buffers of exactly the sizes the call's documented
 // contract gives them, so AddressSanitizer reports any row a kernel would address outside its
 // buffer, whatever the device-side tables hold.  No arithmetic of the method happens here.
+#include <algorithm>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
+#include <vector>
 
 #include "pic_internal.h"
 
@@ -499,18 +501,44 @@ hipError_t launch_decode_bf16(const AttnShape& s, const bf16_t* q, const bf16_t*
   const int64_t rows_all = (int64_t)s.n_layers * s.batch * s.n_q_heads * n_splits;
   float* ws_o = static_cast<float*>(workspace);
   float* ws_ml = ws_o ? ws_o + rows_all * s.head_dim : nullptr;
-  int32_t chunk = (max_len + n_splits - 1) / n_splits;
-  chunk = (chunk + kDecodeWaves * kTile - 1) / (kDecodeWaves * kTile) * (kDecodeWaves * kTile);
+  // ranges per request: dealt by length, or n_splits equal ones of the longest context
+  const bool dealt = decode_dealt(n_splits, s.batch, max_len);
+  int32_t chunk = decode_units(ceil_div(max_len, n_splits)) * kDecodeUnit;
+  std::vector<int32_t> mine(s.batch, n_splits), first(s.batch + 1, 0);
+  if (dealt) {
+    std::vector<int32_t> u(s.batch);
+    int32_t total = 0, longest = 0;
+    for (int b = 0; b < s.batch; ++b) {
+      u[b] = decode_units(std::min(clamp_len(base_len[b], max_base) + step + 1, s.cache_cap));
+      total += u[b];
+      longest = std::max(longest, u[b]);
+    }
+    const RangeCandidates rc = decode_range_candidates(total, longest, n_splits, s.batch);
+    int32_t c = 0;
+    for (int i = 0; i < kDecodeDealt; ++i) {
+      c = rc.at(i);
+      int64_t sum = 0;
+      for (int b = 0; b < s.batch; ++b) sum += ceil_div(u[b], c);
+      if (sum <= (int64_t)n_splits * s.batch) break;
+      if (i == kDecodeDealt - 1) return hipErrorInvalidValue;   // the last candidate always fits
+    }
+    chunk = c * kDecodeUnit;
+    for (int b = 0; b < s.batch; ++b) mine[b] = ceil_div(u[b], c);
+  }
+  for (int b = 0; b < s.batch; ++b) first[b + 1] = first[b] + mine[b];
   const int n_rep = s.n_q_heads / s.n_kv_heads;
   const int groups = decode_head_groups(s);
   for (int l = 0; l < s.n_layers; ++l)
     for (int x = 0; x < groups * n_splits * s.batch * s.n_kv_heads; ++x) {
-      const int hgrp = x % groups, split = (x / groups) % n_splits, bg = x / (groups * n_splits);
+      const int hgrp = x % groups, at = x / groups;
+      int b = 0;
+      while (b < s.batch && at >= first[b + 1] * s.n_kv_heads) ++b;
+      if (b == s.batch) continue;   // more workgroups than ranges
+      const int in_b = at - first[b] * s.n_kv_heads, g = in_b / mine[b], split = in_b % mine[b];
       const int rep0 = 16 * hgrp, n_here = std::min(16, n_rep - rep0);
-      const int b = bg / s.n_kv_heads, g = bg % s.n_kv_heads;
       const int p = clamp_len(base_len[b], max_base) + step;
       const int n_vis = std::min(p + 1, s.cache_cap);
-      const int wc0 = std::min(split * chunk, n_vis), wc1 = std::min(wc0 + chunk, n_vis);
+      const int wc0 = (int)std::min<int64_t>((int64_t)split * chunk, n_vis), wc1 = (int)std::min<int64_t>((int64_t)wc0 + chunk, n_vis);
       const int64_t bh_kv = ((int64_t)l * s.batch + b) * s.n_kv_heads + g;
       if (hgrp == 0 && p < s.cache_cap && p >= wc0 && p < wc1) {
         rd_row(k_new, bh_kv, rb);
@@ -537,10 +565,11 @@ hipError_t launch_decode_bf16(const AttnShape& s, const bf16_t* q, const bf16_t*
       }
       for (int n = 0; n < n_here; ++n) {
         const int64_t row = ((int64_t)l * s.batch + b) * s.n_q_heads + g * n_rep + rep0 + n;
-        if (n_splits == 1) {
+        if (mine[b] == 1) {
           wr_row(out, row, rb);
         } else {
-          const int64_t slot = row * n_splits + split;
+          const int64_t slot = ((int64_t)l * s.batch * n_splits + first[b]) * s.n_q_heads +
+                               (int64_t)(g * n_rep + rep0 + n) * mine[b] + split;
           emu::wr(ws_o, slot, s.head_dim);
           emu::wr(ws_ml, slot, 2);
         }
@@ -549,9 +578,13 @@ hipError_t launch_decode_bf16(const AttnShape& s, const bf16_t* q, const bf16_t*
   if (n_splits == 1) return hipSuccess;
   ++emu::launches;   // the split combine
   for (int64_t row = 0; row < (int64_t)s.n_layers * s.batch * s.n_q_heads; ++row) {
-    for (int sp = 0; sp < n_splits; ++sp) {
-      emu::rd(ws_ml, row * n_splits + sp, 2);
-      emu::rd(ws_o, row * n_splits + sp, s.head_dim);
+    const int h = (int)(row % s.n_q_heads), b = (int)(row / s.n_q_heads % s.batch);
+    const int64_t l = row / s.n_q_heads / s.batch;
+    if (mine[b] == 1) continue;   // stored by its only range
+    for (int sp = 0; sp < mine[b]; ++sp) {
+      const int64_t slot = (l * s.batch * n_splits + first[b]) * s.n_q_heads + (int64_t)h * mine[b] + sp;
+      emu::rd(ws_ml, slot, 2);
+      emu::rd(ws_o, slot, s.head_dim);
     }
     wr_row(out, row, rb);
   }
