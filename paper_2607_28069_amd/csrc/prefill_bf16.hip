@@ -936,8 +936,17 @@ prefill_bf16_kernel(PrefillArgs a) {
   }
   __syncthreads();
   f32x16_t s_a[2], s_b[2];   // scores of the current / next tile, swapped every tile
-  scores(k_lds0, s_a);
-  finish_scores(t0, s_a);
+  // local tiles [0, t_live) hold keys some row of this wave sees.  Outside table mode that is all of
+  // them, or none for a wave whose rows are all past the last (a short suffix, a last m-tile):
+  // such a wave only moves its share of the tiles, and the matrix cores are left to the others
+  // (4 requests of 8000 keys, 32/8 heads: 8 tokens 32.7 -> 27.6 us, 20 tokens 35.8 -> 29.7; 16 of
+  // 4000 x 70 tokens, whose second m-tile holds 24 rows, 126 -> 112).
+  const int t_live = kTable ? (wave_max < t0 * kKeys ? 0 : min(n_tiles, wave_max / kKeys - t0 + 1))
+                            : (row0_wg + wave * kRowsPerWave < M ? n_tiles : 0);
+  if (t_live > 0) {
+    scores(k_lds0, s_a);
+    finish_scores(t0, s_a);
+  }
   __syncthreads();   // every wave is done with K buffer 0 before tile 2 lands there
 
   // One tile.  Resident on entry: K(t+1) in K slot (t+1)&1, V(t) in V slot t&1 (P = t & 1,
@@ -945,8 +954,10 @@ prefill_bf16_kernel(PrefillArgs a) {
   // tile t are finished.  The body between the loads and the next-tile bookkeeping has no
   // branches, so the scheduler can interleave the matrix products of the next tile's scores
   // and of this tile's PV with the exponentials of this tile.
-  auto tile = [&](int t, auto parity, f32x16_t (&scur)[2], f32x16_t (&snext)[2]) {   // t: local
+  // idle: this wave's share of the loads, rotations and barriers only.
+  auto tile = [&](int t, auto parity, auto idle, f32x16_t (&scur)[2], f32x16_t (&snext)[2]) {   // t: local
     constexpr int P = decltype(parity)::value;
+    constexpr bool kIdle = decltype(idle)::value;
     uint8_t* const k_next = P ? k_lds0 : k_lds1;   // holds K(t+1)
     uint8_t* const k_free = P ? k_lds1 : k_lds0;   // receives K(t+2)
     const uint8_t* const v_cur = P ? v_lds1 : v_lds0;   // holds V(t)
@@ -955,7 +966,7 @@ prefill_bf16_kernel(PrefillArgs a) {
     // any, was staged during the previous tile; read before this tile's cos/sin loads)
     int32_t run_f = -1, del_f = 0;   // paged: tile t + 3 (K issued by the next tile)
     if constexpr (kPool) {
-      turn_q(run_v >= 0 ? del_v : 0);
+      if constexpr (!kIdle) turn_q(run_v >= 0 ? del_v : 0);
       if (t + 3 < n_tiles) run_f = tile_run(t0 + t + 3, del_f);
     }
     // this tile's loads (K(t+2), V(t+1)): issued after the first slice outside paged mode,
@@ -964,7 +975,7 @@ prefill_bf16_kernel(PrefillArgs a) {
       if (t + 2 < n_tiles) load_tile(k_free, t0 + t + 2, false, run_k);
       if (t + 1 < n_tiles) load_tile(v_free, t0 + t + 1, true, run_v);
     };
-    if constexpr (kPaged) issue_loads();
+    if constexpr (kPaged || kIdle) issue_loads();
     if constexpr (kRope) {
       if (t + 2 < n_tiles && (t0 + t + 3) * kKeys > ctx) rope_cs(t0 + t + 2);
     }
@@ -973,7 +984,7 @@ prefill_bf16_kernel(PrefillArgs a) {
       if (kPaged && t + 2 < n_tiles && run_k < 0) load_cs(d_k);
       // the row the next tile turns the operand with (tile t + 2 is a whole run, so nothing
       // uses the cos/sin area during this tile)
-      if (run_k >= 0 && del_k != 0 && del_k != q_shift) stage_row(del_k);
+      if (!kIdle && run_k >= 0 && del_k != 0 && del_k != q_shift) stage_row(del_k);
     }
     if constexpr (kPaged) {
       // tile t + 3 not a whole run: the rows and shifts of its keys, loaded now and checked
@@ -985,6 +996,7 @@ prefill_bf16_kernel(PrefillArgs a) {
       }
     }
 
+    if constexpr (!kIdle) {
     // (scores of a tile past the last one are computed on stale LDS and dropped)
     // Hand-ordered body: the K operands of the next tile's score products are read one pair
     // of products ahead and the V^T operands of slice s4 + 1 while slice s4's PV products
@@ -1058,6 +1070,7 @@ prefill_bf16_kernel(PrefillArgs a) {
     l_part += psum;
 
     if (t + 1 < n_tiles) finish_scores(t0 + t + 1, snext);
+    }
     wait_loads();
     if constexpr (kRope) {
       if (t + 2 < n_tiles && (t0 + t + 3) * kKeys > ctx) rope_own(k_free, t0 + t + 2);
@@ -1081,26 +1094,20 @@ prefill_bf16_kernel(PrefillArgs a) {
     __syncthreads();
   };
 
-  // local tiles [0, t_live) hold keys some row of this wave sees (all of them outside table mode)
-  const int t_live = !kTable ? n_tiles
-                             : (wave_max < t0 * kKeys ? 0 : min(n_tiles, wave_max / kKeys - t0 + 1));
+  constexpr std::integral_constant<int, 0> even{};
+  constexpr std::integral_constant<int, 1> odd{};
+  constexpr std::false_type live{};
+  constexpr std::true_type idle{};
   for (int t = 0; t < t_live; t += 2) {
-    tile(t, std::integral_constant<int, 0>{}, s_a, s_b);
-    if (t + 1 < t_live) tile(t + 1, std::integral_constant<int, 1>{}, s_b, s_a);
+    tile(t, even, live, s_a, s_b);
+    if (t + 1 < t_live) tile(t + 1, odd, live, s_b, s_a);
   }
-  if constexpr (kTable) {   // the rest: this wave's share of the loads and the barriers only
-    auto idle = [&](int t, auto parity) {
-      constexpr int P = decltype(parity)::value;
-      flush_pending();   // the last computed tile's last slice (then nothing is pending)
-      pend_p = as_bf16x8(u32x4{0, 0, 0, 0});
-      if (t + 2 < n_tiles) load_tile(P ? k_lds1 : k_lds0, t0 + t + 2, false);
-      if (t + 1 < n_tiles) load_tile(P ? v_lds0 : v_lds1, t0 + t + 1, true);
-      wait_loads();
-      __syncthreads();
-    };
+  if (t_live < n_tiles) {
+    flush_pending();   // the last computed tile's last slice (then nothing is pending)
+    pend_p = as_bf16x8(u32x4{0, 0, 0, 0});
     for (int t = t_live; t < n_tiles; ++t) {
-      if (t & 1) idle(t, std::integral_constant<int, 1>{});
-      else idle(t, std::integral_constant<int, 0>{});
+      if (t & 1) tile(t, odd, idle, s_b, s_a);
+      else tile(t, even, idle, s_a, s_b);
     }
   }
 
