@@ -234,7 +234,9 @@ pic_status pic_compose_shared(const pic_model* model, const void* pool_k, const 
      ctx_len [device, batch]  composed lengths; entries are clamped to [0, max_ctx]
      max_ctx [host]           bound on ctx_len; max_ctx + n_suffix <= cache_cap
      scale                    softmax scale; 0 means 1/sqrt(head_dim)
-     workspace                pic_prefill_workspace_bytes(...) bytes (may be 0 bytes)
+     workspace                pic_prefill_workspace_bytes(...) bytes (may be 0 bytes); a call that
+                              fills half the GPU (128 or more units of 256 packed query rows)
+                              and brings less runs with fewer or no key-range splits
    The prefill kernels (this call and 3a-3c) address one cache stream [cache_cap][D], one
    request's suffix rows [n_suffix][Hkv][D] and one pool head [pool_tokens][D] with 32-bit byte
    offsets: each of cache_cap, n_suffix * Hkv and pool_tokens must be below 2^24

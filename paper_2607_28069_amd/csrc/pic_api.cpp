@@ -115,6 +115,17 @@ pic_status check_attn_model(const pic_model* m) { return check_model(m); }
 bool mfma_prefill(const pic_model* m) { return m->dtype == PIC_BF16; }
 bool mfma_decode(const pic_model* m) { return m->dtype == PIC_BF16; }
 
+// The workspace a prefill of n_suffix tokens after max_ctx needs: what the query call says, except
+// for launches that fill half the GPU, which run unsplit without it.
+pic_status check_prefill_workspace(const pic_model* m, int32_t batch, int32_t n_suffix, int32_t max_ctx, size_t ws_bytes) {
+  if (!mfma_prefill(m)) return PIC_OK;
+  const pic::AttnShape s = shape_of(m, batch, max_ctx + n_suffix, 0.f);
+  const size_t need = pic::prefill_bf16_workspace(s, n_suffix, max_ctx);
+  if (ws_bytes < need && !pic::prefill_bf16_may_run_whole(s, n_suffix))
+    return fail(PIC_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", need, ws_bytes);
+  return PIC_OK;
+}
+
 // Attention over a float32 cache: n_q query rows per request at the positions `pos` gives them.
 // k_new / v_new: the call's own tokens, to be stored too (NULL: already in the cache).
 pic_status launch_f32(const pic::AttnShape& s, const void* q, const void* k_new, const void* v_new, void* ck, void* cv,
@@ -518,9 +529,8 @@ PIC_API pic_status pic_suffix_prefill_attn(const pic_model* model, const void* q
   PIC_CHECK(check_ptr(cache_v, "cache_v"));
   PIC_CHECK(check_ptr(out, "out"));
   if (!ctx_len) return fail(PIC_ERR_INVALID_ARG, "ctx_len is NULL");
-  const size_t need = pic_prefill_workspace_bytes(model, batch, n_suffix, max_ctx);
-  if (need > 0 && (workspace == nullptr || ws_bytes < need))
-    return fail(PIC_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", need, ws_bytes);
+  if (workspace == nullptr) ws_bytes = 0;
+  PIC_CHECK(check_prefill_workspace(model, batch, n_suffix, max_ctx, ws_bytes));
   const hipStream_t st = (hipStream_t)stream;
   const pic::AttnShape s = shape_of(model, batch, cache_cap, scale);
   // a4: both kernels store the suffix K/V into slots [ctx, ctx + n_suffix) (App. C.1: inline
@@ -578,9 +588,8 @@ PIC_API pic_status pic_suffix_prefill_attn_rope(const pic_model* model, const vo
   PIC_CHECK(check_ptr(table, "table"));
   PIC_CHECK(check_ptr(out, "out"));
   if (!ctx_len) return fail(PIC_ERR_INVALID_ARG, "ctx_len is NULL");
-  const size_t need = pic_prefill_workspace_bytes(model, batch, n_suffix, max_ctx);
-  if (need > 0 && (workspace == nullptr || ws_bytes < need))
-    return fail(PIC_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", need, ws_bytes);
+  if (workspace == nullptr) ws_bytes = 0;
+  PIC_CHECK(check_prefill_workspace(model, batch, n_suffix, max_ctx, ws_bytes));
   const pic::AttnShape s = shape_of(model, batch, cache_cap, scale);
   const int64_t stride = n_tables(model) > 1 ? (int64_t)(max_abs_delta + 1) * (model->head_dim / 2) : 0;
   return hip_status(pic::launch_prefill_bf16_rope(
@@ -695,9 +704,8 @@ PIC_API pic_status pic_paged_prefill_attn(const pic_model* model, const void* po
   // call reads whole runs from the pool and every other tile from the cache
   if (!slot_src && !tile_map) return fail(PIC_ERR_INVALID_ARG, "slot map is NULL (allowed only with a tile map)");
   if (!ctx_len) return fail(PIC_ERR_INVALID_ARG, "ctx_len is NULL");
-  const size_t need = pic_prefill_workspace_bytes(model, batch, n_suffix, max_ctx);
-  if (need > 0 && (workspace == nullptr || ws_bytes < need))
-    return fail(PIC_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", need, ws_bytes);
+  if (workspace == nullptr) ws_bytes = 0;
+  PIC_CHECK(check_prefill_workspace(model, batch, n_suffix, max_ctx, ws_bytes));
   const pic::AttnShape s = shape_of(model, batch, cache_cap, scale);
   const int64_t stride = n_tables(model) > 1 ? (int64_t)(max_abs_delta + 1) * (model->head_dim / 2) : 0;
   return hip_status(pic::launch_prefill_bf16_paged(
@@ -749,9 +757,8 @@ PIC_API pic_status pic_frontier_prefill_attn(const pic_model* model, const void*
   PIC_CHECK(check_ptr(out, "out"));
   if (!pos) return fail(PIC_ERR_INVALID_ARG, "pos is NULL");
   if (!n_valid) return fail(PIC_ERR_INVALID_ARG, "n_valid is NULL");
-  const size_t need = pic_frontier_workspace_bytes(model, batch, n_inline, max_len);
-  if (need > 0 && (workspace == nullptr || ws_bytes < need))
-    return fail(PIC_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", need, ws_bytes);
+  if (workspace == nullptr) ws_bytes = 0;
+  PIC_CHECK(check_prefill_workspace(model, batch, n_inline, max_len > n_inline ? max_len - n_inline : 0, ws_bytes));
   const hipStream_t st = (hipStream_t)stream;
   const pic::AttnShape s = shape_of(model, batch, cache_cap, scale);
   pic::RowPos rp;

@@ -92,11 +92,15 @@ constexpr int kDecodeWaves = 4;            // waves per decode workgroup
 constexpr int kDecodeMinWaveKeys = 64;     // fewest keys a decode wave is given
 
 // Key-range split of a prefill launch: m-tiles of query rows, splits per (m-tile, request,
-// kv head) and key tiles per split.
+// kv head), key tiles per split, and whether the splits leave their outputs in float32 (else
+// bf16).  The best plan whose partials fit in ws_bytes.
 struct SplitPlan {
   int m_tiles, n_splits, tiles_per_split;
+  bool f32_partials;
 };
-SplitPlan plan_prefill_splits(const AttnShape& s, int32_t n_suffix, int32_t max_ctx);
+SplitPlan plan_prefill_splits(const AttnShape& s, int32_t n_suffix, int32_t max_ctx, size_t ws_bytes);
+// Bytes of partials per split and query row: the split's output and its (max, sum).
+inline size_t prefill_partial_bytes(int head_dim, bool f32) { return (size_t)head_dim * (f32 ? 4 : 2) + 2 * sizeof(float); }
 
 // Attention over float32 caches.  Rows [L][B][n_q][Hq]: query token i of request b sits at
 // position pos(b, i) and sees slots [0, that position]; rows without a position are left
@@ -118,6 +122,8 @@ struct F32AttnArgs {
 hipError_t launch_attn_f32(const F32AttnArgs& a);
 
 size_t prefill_bf16_workspace(const AttnShape& s, int32_t n_suffix, int32_t max_ctx);
+// Launches that may bring less than that: they then run the best plan that fits, or unsplit.
+bool prefill_bf16_may_run_whole(const AttnShape& s, int32_t n_suffix);
 // Also writes k_suf / v_suf into cache slots [ctx_len[b], ctx_len[b] + n_suffix).
 hipError_t launch_prefill_bf16(const AttnShape& s, const bf16_t* q, const bf16_t* k_suf,
                                const bf16_t* v_suf, bf16_t* cache_k, bf16_t* cache_v,

@@ -5,49 +5,102 @@
 
 namespace pic {
 
-// Key-range splits of the prefill.  A launch whose (m-tile, request, kv head) units already
-// occupy half the 256 compute units is not split: under load the chip runs at its power limit,
-// where busy units speed up as others idle, so the last round's idle units cost little and the
-// partials and the combine cost more (measured: 224 units of the 32K Qwen workload 898 us
-// unsplit against 921 us in 8 key ranges; the frontier workload's 1152 units 900 against
-// 934 us in 2).  Smaller launches are split so that they cover the compute units in whole
-// rounds, each split keeping at least 8 key tiles.  Cost in units of one workgroup-tile
-// (~2 us): rounds * tiles per split, plus, for split runs, one tile (the combine launch; the
-// splits' own prologues run in parallel) and the partials each split writes and the combine
-// reads back (bf16 output and fp32 (max, sum): 264 bytes per query row, twice, at ~4 TB/s).  Ties (within 3%) go to
-// fewer splits.
-SplitPlan plan_prefill_splits(const AttnShape& s, int32_t n_suffix, int32_t max_ctx) {
-  SplitPlan p;
+namespace {
+
+int64_t prefill_m_tiles(const AttnShape& s, int32_t n_suffix) {
   const int64_t M = (int64_t)n_suffix * (s.n_q_heads / s.n_kv_heads);
-  p.m_tiles = (int)((M + kPrefillRowsPerWG - 1) / kPrefillRowsPerWG);
-  const int64_t base = (int64_t)p.m_tiles * s.batch * s.n_kv_heads * s.n_layers;
-  const double rows = (double)s.n_layers * s.batch * n_suffix * s.n_q_heads;
-  const int tiles = (int)(((int64_t)max_ctx + n_suffix + kPrefillKeys - 1) / kPrefillKeys);
+  return (M + kPrefillRowsPerWG - 1) / kPrefillRowsPerWG;
+}
+int64_t prefill_rows(const AttnShape& s, int32_t n_suffix) {
+  return (int64_t)s.n_layers * s.batch * n_suffix * s.n_q_heads;
+}
+int prefill_tiles(int32_t n_suffix, int32_t max_ctx) {
+  return (int)(((int64_t)max_ctx + n_suffix + kPrefillKeys - 1) / kPrefillKeys);
+}
+
+int64_t prefill_units(const AttnShape& s, int32_t n_suffix) {
+  return prefill_m_tiles(s, n_suffix) * s.batch * s.n_kv_heads * s.n_layers;
+}
+
+// A launch whose units fill half the compute units or whose key ranges would be shorter than 8
+// tiles needs no workspace: it can run whole, its sums in float32 from end to end (and keeps them
+// so, with float32 partials, where the plan below splits it).  Any other brings bf16 partials for
+// this count, which covers the compute units in whole rounds at the least rounds * tiles, one tile
+// for the combine launch and the partial traffic counted in (ties within 3% go to fewer).
+int prefill_bf16_splits_held(const AttnShape& s, int32_t n_suffix, int32_t max_ctx) {
+  const int64_t base = prefill_units(s, n_suffix);
+  if (base >= 128) return 1;
+  const double rows = (double)prefill_rows(s, n_suffix);
+  const int tiles = prefill_tiles(n_suffix, max_ctx);
   int best = 1;
   double best_cost = 1e30;
-  for (int sp = 1; sp <= (base >= 128 ? 1 : kPrefillMaxSplits); ++sp) {
+  for (int sp = 1; sp <= kPrefillMaxSplits; ++sp) {
     const int tps = (tiles + sp - 1) / sp;
     if (sp > 1 && tps < 8) break;
     const int64_t rounds = (base * sp + 255) / 256;
-    const double partials = sp > 1 ? 1.0 + sp * rows * 2.0 * (s.head_dim * 2 + 8) / 4e12 / 2e-6 : 0.0;
+    const double partials = sp > 1 ? 1.0 + sp * rows * 2.0 * (double)prefill_partial_bytes(s.head_dim, false) / 4e12 / 2e-6 : 0.0;
     const double cost = (double)rounds * tps + partials;
     if (cost < best_cost * 0.97) {
       best_cost = cost;
       best = sp;
     }
   }
+  return best;
+}
+
+}  // namespace
+
+// Key-range splits of the prefill, by estimated time in us.  Under load the chip sits at its power
+// limit, where a busy compute unit runs slower the more of them are busy: a workgroup's 64-key
+// tile takes t_few with up to half of them busy and t_full with all (measured: 16 to 128
+// workgroups 1.35 us, 192 1.65, 256 2.0; up to 128 rows the loads bound it, 1.15 us; at head_dim
+// 64 1.0 and 1.2 us).  A split run adds the combine launch (5 us, a little more for each split) and
+// the partials, written and read at ~5 TB/s; the split that ends in the suffix has dearer tiles
+// (rows addressed one by one, masked, perhaps turned) and is better one that is not full.  Ties go
+// to fewer splits.  Measured, whole / as planned: 8 requests of 10K keys x 128 tokens (128 units)
+// 225 / 175 us, of 4K 98 / 84; 16 of 4K x 16 tokens 81 / 61; 4 of 32K, 28/4 heads x 256 tokens (112
+// units) 434 us in 9 splits / 420 in 2.  256 units stay whole.
+SplitPlan plan_prefill_splits(const AttnShape& s, int32_t n_suffix, int32_t max_ctx, size_t ws_bytes) {
+  SplitPlan p;
+  const int held = prefill_bf16_splits_held(s, n_suffix, max_ctx);
+  const int64_t base = prefill_units(s, n_suffix);
+  p.m_tiles = (int)prefill_m_tiles(s, n_suffix);
+  p.f32_partials = held == 1;
+  const double split_bytes = (double)prefill_rows(s, n_suffix) * (double)prefill_partial_bytes(s.head_dim, p.f32_partials);
+  const double room = held > 1 ? held * split_bytes : (base >= 128 ? (double)ws_bytes : 0.0);
+  const int tiles = prefill_tiles(n_suffix, max_ctx);
+  const bool narrow = (int64_t)n_suffix * (s.n_q_heads / s.n_kv_heads) <= 128;
+  const double t_few = s.head_dim == 64 ? 1.0 : (narrow ? 1.15 : 1.36);
+  const double t_full = s.head_dim == 64 || narrow ? 1.2 : 2.0;
+  auto tile_us = [&](int64_t active) { return active <= 128 ? t_few : t_few + (t_full - t_few) * (double)(active - 128) / 128.0; };
+  auto range = [&](int sp) { return (tiles + sp - 1) / sp; };
+  auto cost = [&](int sp) {
+    const int64_t wgs = base * sp;
+    const double us = range(sp) * ((double)(wgs / 256) * t_full + (wgs % 256 ? tile_us(wgs % 256) : 0.0));
+    return sp == 1 ? us : us + 5.0 + 0.3 * sp + 2.0 * sp * split_bytes / 5e6 + (sp * range(sp) == tiles ? 1.0 : 0.0);
+  };
+  int best = 1;
+  double best_us = cost(1);
+  for (int sp = 2; sp <= kPrefillMaxSplits && sp * split_bytes <= room; ++sp) {
+    if ((tiles + range(sp) - 1) / range(sp) < sp) continue;   // (the same ranges as fewer splits)
+    if (cost(sp) < best_us * 0.99) {
+      best = sp;
+      best_us = cost(sp);
+    }
+  }
+  // (short launches: what the estimate cannot tell apart, machines of other clocks do)
+  if (held > 1 && best_us < 100.0 && cost(held) < best_us + 2.0) best = held;
   p.n_splits = best;
-  p.tiles_per_split = (tiles + best - 1) / best;
+  p.tiles_per_split = range(best);
   return p;
 }
 
 size_t prefill_bf16_workspace(const AttnShape& s, int32_t n_suffix, int32_t max_ctx) {
-  const SplitPlan p = plan_prefill_splits(s, n_suffix, max_ctx);
-  if (p.n_splits == 1) return 0;
-  // per split and query row: the split's normalised output (bf16) and its (max, sum) pair
-  const size_t rows = (size_t)s.n_layers * s.batch * n_suffix * s.n_q_heads;
-  return (size_t)p.n_splits * rows * (s.head_dim * 2 + 2 * sizeof(float));
+  const SplitPlan p = plan_prefill_splits(s, n_suffix, max_ctx, SIZE_MAX);
+  return p.n_splits == 1 ? 0 : (size_t)p.n_splits * prefill_rows(s, n_suffix) * prefill_partial_bytes(s.head_dim, p.f32_partials);
 }
+
+bool prefill_bf16_may_run_whole(const AttnShape& s, int32_t n_suffix) { return prefill_units(s, n_suffix) >= 128; }
 
 int32_t slot_map_tiles(int32_t map_cap) { return (int32_t)(((int64_t)map_cap + kPrefillKeys - 1) / kPrefillKeys); }
 

@@ -170,7 +170,8 @@ struct PrefillArgs {
   int32_t tiles_per_split;  // key tiles per split
   int32_t n_wg;             // m_tiles * n_splits * batch * n_kv_heads
   int64_t rows_total;       // L * batch * n_suffix * Hq (query rows of one split's partials)
-  bf16_t* ws_o;             // [n_splits][rows_total][D] each split's normalised output
+  void* ws_o;               // [n_splits][rows_total][D] each split's normalised output, bf16 or
+  int32_t f32_partials;     // float32
   float2* ws_ml;            // [n_splits][rows_total] (reference max, row sum)
   float scale_log2;
 };
@@ -1118,17 +1119,27 @@ prefill_bf16_kernel(PrefillArgs a) {
   // normalised and rounded to bf16: the output, or one split's share of it (with its reference
   // max and row sum, the weights the combine needs)
   const float inv = 1.f / l_tot;
-  bf16_t* op = a.n_splits == 1 ? a.out + orow * kHD : a.ws_o + (split * a.rows_total + orow) * kHD;
+  if (a.n_splits > 1 && a.f32_partials) {
+    float* op = static_cast<float*>(a.ws_o) + (split * a.rows_total + orow) * kHD;
 #pragma unroll
-  for (int db = 0; db < kDB; ++db)
+    for (int db = 0; db < kDB; ++db)
 #pragma unroll
-    for (int qd = 0; qd < 4; ++qd) {
-      const int d = 32 * db + 8 * qd + 4 * hh;
-      uint2 v;
-      v.x = pack_bf16x2(oacc[db][4 * qd] * inv, oacc[db][4 * qd + 1] * inv);
-      v.y = pack_bf16x2(oacc[db][4 * qd + 2] * inv, oacc[db][4 * qd + 3] * inv);
-      *reinterpret_cast<uint2*>(op + d) = v;
-    }
+      for (int qd = 0; qd < 4; ++qd)
+        *reinterpret_cast<float4*>(op + 32 * db + 8 * qd + 4 * hh) =
+            make_float4(oacc[db][4 * qd] * inv, oacc[db][4 * qd + 1] * inv, oacc[db][4 * qd + 2] * inv, oacc[db][4 * qd + 3] * inv);
+  } else {
+    bf16_t* op = a.n_splits == 1 ? a.out + orow * kHD : static_cast<bf16_t*>(a.ws_o) + (split * a.rows_total + orow) * kHD;
+#pragma unroll
+    for (int db = 0; db < kDB; ++db)
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd) {
+        const int d = 32 * db + 8 * qd + 4 * hh;
+        uint2 v;
+        v.x = pack_bf16x2(oacc[db][4 * qd] * inv, oacc[db][4 * qd + 1] * inv);
+        v.y = pack_bf16x2(oacc[db][4 * qd + 2] * inv, oacc[db][4 * qd + 3] * inv);
+        *reinterpret_cast<uint2*>(op + d) = v;
+      }
+  }
   if (a.n_splits > 1 && hh == 0) a.ws_ml[split * a.rows_total + orow] = make_float2(m_run, l_tot);
 }
 
@@ -1142,8 +1153,8 @@ prefill_bf16_kernel(PrefillArgs a) {
 // kBatch: splits whose loads are issued together (4, 8 or 16, the smallest that covers n_splits:
 // a larger batch holds more registers and lowers the occupancy that few splits need)
 constexpr int kCombineRowsPerWG = 16;
-template <int HD, int kCombineBatch>
-__global__ void __launch_bounds__(256) prefill_combine_kernel(const bf16_t* __restrict__ ws_o,
+template <int HD, int kCombineBatch, typename PT>
+__global__ void __launch_bounds__(256) prefill_combine_kernel(const PT* __restrict__ ws_o,
                                                               const float2* __restrict__ ws_ml,
                                                               int32_t n_splits, int64_t rows_total,
                                                               const int32_t* __restrict__ n_valid,
@@ -1151,6 +1162,7 @@ __global__ void __launch_bounds__(256) prefill_combine_kernel(const bf16_t* __re
                                                               int32_t batch,
                                                               bf16_t* __restrict__ out) {
   constexpr int kLanes = HD / 8;   // lanes per row
+  constexpr int kPieces = sizeof(PT) / 2;   // 16-byte pieces of a lane's 8 head dims
   const int64_t row = (int64_t)blockIdx.x * kCombineRowsPerWG + threadIdx.x / kLanes;
   if (row >= rows_total) return;
   if (n_valid) {   // row = ((l * B + b) * n_q + i) * Hq + h
@@ -1165,30 +1177,39 @@ __global__ void __launch_bounds__(256) prefill_combine_kernel(const bf16_t* __re
   float M = -INFINITY, den = 0.f, o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int s0 = 0; s0 < n_splits; s0 += kCombineBatch) {
     float2 mls[kCombineBatch];
-    uint4 xs[kCombineBatch];
+    uint4 xs[kCombineBatch][kPieces];
 #pragma unroll
     for (int u = 0; u < kCombineBatch; ++u) {
       const int64_t s = s0 + u;
       mls[u] = s < n_splits ? ws_ml[s * rows_total + row] : make_float2(-INFINITY, 0.f);
-      xs[u] = s < n_splits ? *reinterpret_cast<const uint4*>(ws_o + (s * rows_total + row) * HD + d)
-                           : uint4{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int i = 0; i < kPieces; ++i)
+        xs[u][i] = s < n_splits ? reinterpret_cast<const uint4*>(ws_o + (s * rows_total + row) * HD + d)[i]
+                                : uint4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
   for (int u = 0; u < kCombineBatch; ++u) {
     const float2 ml = mls[u];
-    const uint4 x = xs[u];
     const bool seen = ml.x != -INFINITY;
     const float m_new = seen ? fmaxf(M, ml.x) : M;
     const float keep = seen ? __builtin_amdgcn_exp2f(M - m_new) : 1.f;   // 0 while M is -inf
     const float w = seen ? __builtin_amdgcn_exp2f(ml.x - m_new) * ml.y : 0.f;
     M = m_new;
     den = den * keep + w;
-    const uint32_t xw[4] = {x.x, x.y, x.z, x.w};
+    float x[8];
+    if constexpr (kPieces == 1) {
+      unpack8(u32x4{xs[u][0].x, xs[u][0].y, xs[u][0].z, xs[u][0].w}, x);
+    } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      o[2 * e] = o[2 * e] * keep + (seen ? w * __uint_as_float(xw[e] << 16) : 0.f);
-      o[2 * e + 1] = o[2 * e + 1] * keep + (seen ? w * __uint_as_float(xw[e] & 0xFFFF0000u) : 0.f);
+      for (int i = 0; i < 2; ++i) {
+        x[4 * i] = __uint_as_float(xs[u][i].x);
+        x[4 * i + 1] = __uint_as_float(xs[u][i].y);
+        x[4 * i + 2] = __uint_as_float(xs[u][i].z);
+        x[4 * i + 3] = __uint_as_float(xs[u][i].w);
+      }
     }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = o[e] * keep + (seen ? w * x[e] : 0.f);
   }
   }
   const float inv = 1.f / den;
@@ -1282,15 +1303,17 @@ hipError_t launch_hd(const AttnShape& s, const PrefillArgs& a, const SplitPlan& 
   const dim3 cgrid((unsigned)((a.rows_total + kCombineRowsPerWG - 1) / kCombineRowsPerWG));
   const dim3 cblock(kCombineRowsPerWG * HD / 8);
   const int32_t* nv = mode == kModeTable ? a.n_valid : nullptr;
-  if (p.n_splits <= 4)
-    hipLaunchKernelGGL((prefill_combine_kernel<HD, 4>), cgrid, cblock, 0, stream, a.ws_o, a.ws_ml, p.n_splits,
-                       a.rows_total, nv, n_q, s.n_q_heads, s.batch, a.out);
-  else if (p.n_splits <= 8)
-    hipLaunchKernelGGL((prefill_combine_kernel<HD, 8>), cgrid, cblock, 0, stream, a.ws_o, a.ws_ml, p.n_splits,
-                       a.rows_total, nv, n_q, s.n_q_heads, s.batch, a.out);
-  else
-    hipLaunchKernelGGL((prefill_combine_kernel<HD, 16>), cgrid, cblock, 0, stream, a.ws_o, a.ws_ml, p.n_splits,
-                       a.rows_total, nv, n_q, s.n_q_heads, s.batch, a.out);
+  auto combine = [&](auto* ws_o, auto batch) {
+    hipLaunchKernelGGL((prefill_combine_kernel<HD, decltype(batch)::value, std::remove_pointer_t<decltype(ws_o)>>), cgrid,
+                       cblock, 0, stream, ws_o, a.ws_ml, p.n_splits, a.rows_total, nv, n_q, s.n_q_heads, s.batch, a.out);
+  };
+  auto combine_as = [&](auto* ws_o) {
+    if (p.n_splits <= 4) combine(ws_o, std::integral_constant<int, 4>{});
+    else if (p.n_splits <= 8) combine(ws_o, std::integral_constant<int, 8>{});
+    else combine(ws_o, std::integral_constant<int, 16>{});
+  };
+  if (p.f32_partials) combine_as(static_cast<float*>(a.ws_o));
+  else combine_as(static_cast<bf16_t*>(a.ws_o));
   return hipGetLastError();
 }
 
@@ -1299,7 +1322,7 @@ hipError_t launch(const AttnShape& s, PrefillArgs a, int mode, bool interleaved,
   const int n_rep = s.n_q_heads / s.n_kv_heads;
   const int64_t M = (int64_t)n_q * n_rep;
   if (M == 0 || s.batch == 0 || s.n_layers == 0) return hipSuccess;
-  const SplitPlan p = plan_prefill_splits(s, n_q, max_ctx);
+  const SplitPlan p = plan_prefill_splits(s, n_q, max_ctx, workspace ? ws_bytes : 0);
   a.n_suffix = n_q;
   a.n_rep = n_rep;
   a.rep_magic = ((uint64_t(1) << 32) + n_rep - 1) / n_rep;
@@ -1313,11 +1336,12 @@ hipError_t launch(const AttnShape& s, PrefillArgs a, int mode, bool interleaved,
   a.tiles_per_split = p.tiles_per_split;
   a.n_wg = p.m_tiles * p.n_splits * s.batch * s.n_kv_heads;
   a.rows_total = (int64_t)s.n_layers * s.batch * n_q * s.n_q_heads;
-  a.ws_o = static_cast<bf16_t*>(workspace);
-  a.ws_ml = a.ws_o ? reinterpret_cast<float2*>(a.ws_o + (size_t)p.n_splits * a.rows_total * s.head_dim) : nullptr;
+  a.ws_o = workspace;
+  a.f32_partials = p.f32_partials;
+  a.ws_ml = workspace ? reinterpret_cast<float2*>(static_cast<char*>(workspace) + (size_t)p.n_splits * a.rows_total * s.head_dim *
+                                                                               (p.f32_partials ? 4 : 2))
+                      : nullptr;
   a.scale_log2 = s.scale_log2;
-  if (p.n_splits > 1 && (workspace == nullptr || ws_bytes < prefill_bf16_workspace(s, n_q, max_ctx)))
-    return hipErrorInvalidValue;
   if (s.head_dim == 64) return launch_hd<64>(s, a, p, mode, interleaved, n_q, stream);
   if (s.head_dim == 128) return launch_hd<128>(s, a, p, mode, interleaved, n_q, stream);
   return hipErrorInvalidValue;

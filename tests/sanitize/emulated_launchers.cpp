@@ -223,17 +223,16 @@ hipError_t prefill_walk(const AttnShape& s, const PrefillEmu& a, int mode, int32
   const int n_rep = s.n_q_heads / s.n_kv_heads;
   const int64_t M = (int64_t)n_q * n_rep;
   if (M == 0 || s.batch == 0 || s.n_layers == 0) return hipSuccess;
-  const SplitPlan p = plan_prefill_splits(s, n_q, max_ctx);
+  const SplitPlan p = plan_prefill_splits(s, n_q, max_ctx, workspace ? ws_bytes : 0);
   if (M >= (int64_t(1) << 27)) return hipErrorInvalidValue;
-  if (p.n_splits > 1 && (workspace == nullptr || ws_bytes < prefill_bf16_workspace(s, n_q, max_ctx)))
-    return hipErrorInvalidValue;
   if (p.n_splits > kPrefillMaxSplits) return hipErrorInvalidValue;
   ++emu::launches;
   const bool table = mode == kModeTable, paged = mode == kModePaged, runs = mode == kModeRuns;
   const bool rope = mode == kModeRope, pool = paged || runs;
   const int64_t rows_total = (int64_t)s.n_layers * s.batch * n_q * s.n_q_heads;
-  bf16_t* ws_o = static_cast<bf16_t*>(workspace);
-  float2* ws_ml = ws_o ? reinterpret_cast<float2*>(ws_o + (size_t)p.n_splits * rows_total * s.head_dim) : nullptr;
+  const int64_t part = (int64_t)s.head_dim * (p.f32_partials ? 4 : 2);   // bytes of one split's row
+  char* ws_o = static_cast<char*>(workspace);
+  float2* ws_ml = ws_o ? reinterpret_cast<float2*>(ws_o + (size_t)p.n_splits * rows_total * part) : nullptr;
   const int64_t rb = (int64_t)s.head_dim * 2, half = s.head_dim / 2;   // bf16 row bytes (128 or 64 dims)
   const int n_wg = p.m_tiles * p.n_splits * s.batch * s.n_kv_heads;
   for (int l = 0; l < s.n_layers; ++l)
@@ -348,7 +347,7 @@ hipError_t prefill_walk(const AttnShape& s, const PrefillEmu& a, int mode, int32
         if (p.n_splits == 1) {
           wr_row(a.out, orow(j), rb);
         } else {
-          wr_row(ws_o, split * rows_total + orow(j), rb);
+          wr_row(ws_o, split * rows_total + orow(j), part);
           wr_row(ws_ml, split * rows_total + orow(j), 8);
         }
       }
@@ -364,7 +363,7 @@ hipError_t prefill_walk(const AttnShape& s, const PrefillEmu& a, int mode, int32
     }
     for (int sp = 0; sp < p.n_splits; ++sp) {
       rd_row(ws_ml, sp * rows_total + row, 8);
-      rd_row(ws_o, sp * rows_total + row, rb);
+      rd_row(ws_o, sp * rows_total + row, part);
     }
     wr_row(a.out, row, rb);
   }
