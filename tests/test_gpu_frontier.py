@@ -128,3 +128,35 @@ def test_frontier_call_equals_suffix_call_on_the_plain_layout():
     torch.cuda.synchronize()
     assert torch.equal(d["cache_k"], ck_a) and torch.equal(d["cache_v"], cv_a)
     assert torch.equal(out_a, out_b)
+
+
+# units per XCD (requests x kv heads / 8 x m-tiles): all pairs m-tile by m-tile (64), only the last
+# round of pairs (144), pairs that do not divide over the XCDs (plain order), head_dim 64
+@pytest.mark.parametrize("batch,hq,hkv,d,n", [(16, 32, 8, 128, 256), (16, 32, 8, 128, 570), (3, 28, 4, 128, 300),
+                                              (8, 8, 2, 64, 200)])
+def test_frontier_dispatch_orders_cover_every_row(batch, hq, hkv, d, n):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    f = lambda *s: torch.randn(s, generator=g, device=DEV, dtype=torch.bfloat16)
+    max_len = 900
+    pos = torch.stack([torch.randperm(max_len, generator=g, device=DEV)[:n].sort().values for _ in range(batch)]).int()
+    nv = torch.tensor([n - 7 * (b % 3) for b in range(batch)], dtype=torch.int32, device=DEV)
+    q, k, v, K, V = f(batch, n, hq, d), f(batch, n, hkv, d), f(batch, n, hkv, d), f(batch, hkv, max_len, d), f(batch, hkv, max_len, d)
+    out = torch.full_like(q, 7.0)
+    m = pic.Model.of(1, hq, hkv, d, "bf16", 5e5)
+    ws = torch.empty(max(pic.pic_frontier_workspace_bytes(m, batch, n, max_len), 16), dtype=torch.uint8, device=DEV)
+    pic.pic_frontier_prefill_attn(m, q, k, v, K, V, batch, max_len, pos, nv, n, max_len, out, ws)
+    torch.cuda.synchronize()
+    rep = hq // hkv
+    for b in range(batch):
+        c = int(nv[b])
+        assert bool((out[b, c:] == 7.0).all())
+        p = pos[b, :c].long()
+        hidden = torch.arange(max_len, device=DEV)[None] > p.repeat_interleave(rep)[:, None]
+        for h in range(hkv):
+            assert torch.equal(K[b, h, p], k[b, :c, h]) and torch.equal(V[b, h, p], v[b, :c, h])
+            qq = q[b, :c, h * rep:(h + 1) * rep].reshape(c * rep, d).double()
+            s = (qq @ K[b, h].double().t().contiguous() / d ** 0.5).masked_fill(hidden, -float("inf"))
+            ref = torch.softmax(s, -1) @ V[b, h].double()
+            got = out[b, :c, h * rep:(h + 1) * rep].reshape(c * rep, d).double()
+            assert bool(((got - ref).abs() <= 2e-2 + 1e-2 * ref.abs()).all()), (b, h)
