@@ -281,10 +281,9 @@ prefill_bf16_kernel(PrefillArgs a) {
   const int r = row0_wg + wave * kRowsPerWave + n;    // this lane's query row
   bool row_ok = r < M;
   const int tok = row_ok ? div_rep(r) : a.n_suffix - 1;
-  const int hq = g * n_rep + (row_ok ? r - div_rep(r) * n_rep : 0);
   // ctx: keys below it come from the cache (suffix mode: the composed context);
   // pos_min_wg / pos_max_wg: nearest / furthest position of this workgroup's query rows
-  int ctx, qpos, pos_min_wg, pos_max_wg;
+  int ctx, qpos, pos_min_wg, pos_max_wg, nv_wg = 0;   // nv_wg: table mode, the request's used tokens
   if constexpr (!kTable) {
     ctx = clamp_len(a.ctx_len[b], a.max_ctx);
     pos_min_wg = ctx + div_rep(row0_wg);
@@ -294,6 +293,7 @@ prefill_bf16_kernel(PrefillArgs a) {
     __shared__ int red_lo[kWaves], red_hi[kWaves];
     int nv = a.n_valid[b];
     nv = nv < 0 ? 0 : (nv > a.n_suffix ? a.n_suffix : nv);
+    nv_wg = nv;
     row_ok = row_ok && tok < nv;
     int p = row_ok ? a.q_pos[(int64_t)b * a.n_suffix + tok] : -1;
     if (row_ok) p = p < 0 ? 0 : (p > a.max_pos ? a.max_pos : p);
@@ -427,18 +427,19 @@ prefill_bf16_kernel(PrefillArgs a) {
       }
     }
   }
-  const int64_t qrow = (((int64_t)l * a.batch + b) * a.n_suffix + tok) * a.n_q_heads + hq;
-
-  const int64_t orow = (((int64_t)l * a.batch + b) * a.n_suffix + tok) * a.n_q_heads + hq;
+  // row of q / out / a split's partials of this request's packed row r2 (token r2 / n_rep)
+  auto row_at = [&](int r2, int tok2) {
+    return (((int64_t)l * a.batch + b) * a.n_suffix + tok2) * a.n_q_heads + g * n_rep + (r2 - tok2 * n_rep);
+  };
   if (n_tiles <= 0) {   // (uniform) a split past this workgroup's last visible key
-    if (a.n_splits > 1 && row_ok && hh == 0) a.ws_ml[split * a.rows_total + orow] = make_float2(-INFINITY, 0.f);
+    if (a.n_splits > 1 && row_ok && hh == 0) a.ws_ml[split * a.rows_total + row_at(r, tok)] = make_float2(-INFINITY, 0.f);
     return;
   }
 
   // ---- Q^T operand: lane (n, hh) holds q[row n][16 ks + 8 hh .. +8) for ks = 0 .. D / 16 - 1
   bf16x8_t qop[kKS];
   {
-    const u32x4* qp = reinterpret_cast<const u32x4*>(a.q + qrow * kHD);
+    const u32x4* qp = reinterpret_cast<const u32x4*>(a.q + (row_ok ? row_at(r, tok) : 0) * kHD);
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks) qop[ks] = as_bf16x8(row_ok ? qp[2 * ks + hh] : u32x4{0, 0, 0, 0});
   }
@@ -1126,32 +1127,67 @@ prefill_bf16_kernel(PrefillArgs a) {
   // ---- lane holds head dims 32 db + 8 qd + 4 hh + (0..3) of its row
   flush_pending();   // the last tile's last slice
   const float l_tot = pair_sum(l_part);
-  if (!row_ok) return;
-  // normalised and rounded to bf16: the output, or one split's share of it (with its reference
-  // max and row sum, the weights the combine needs)
+  const bool wave_rows = __any(row_ok);
+  // (lane number as the epilogue sees it: opaque, so that what follows from it is worked out here
+  // and not held in registers through the key loop)
+  int lane_e = lane;
+  asm volatile("" : "+v"(lane_e));
+  const int n_e = lane_e & 31, hh_e = lane_e >> 5;
+  if (a.n_splits > 1 && hh_e == 0 && row_ok) {
+    const int r2 = row0_wg + wave * kRowsPerWave + n_e;
+    a.ws_ml[split * a.rows_total + row_at(r2, div_rep(r2))] = make_float2(m_run, l_tot);
+  }
+  if (!wave_rows) return;
+  // Normalised: the output in bf16, or one split's share of it in bf16 or float32 (with its
+  // reference max and row sum, the weights the combine needs).  A lane holds 8 bytes here and there
+  // of one row, so the wave's 32 rows go through LDS (the tiles' buffers, free since the last
+  // barrier) and leave as whole rows, 16 bytes per lane.  Stored from the registers, 16 bytes of
+  // 32 rows per instruction, the partials of a lone request (15 splits x 4096 rows) took 9 us of
+  // its 33 us launch.
   const float inv = 1.f / l_tot;
+  uint8_t* const stage = (wave & 4 ? (wave & 2 ? v_lds1 : v_lds0) : (wave & 2 ? k_lds1 : k_lds0)) + (wave & 1) * (kTileBytes / 2);
+  auto chunk_at = [&](int row, int c) { return row * kRowBytes + ((c ^ k_swz<HD>(row)) << 4); };
+  // rows of kRowBytes bytes from the stage to base + row * stride + off (row: of out, or of a split)
+  auto flush_rows = [&](uint8_t* base, int64_t stride, int off) {
+    const int rows_here = M - (row0_wg + wave * kRowsPerWave);
+#pragma unroll
+    for (int i = 0; i < kRowsPerWave / kRowsPerLoad; ++i) {
+      if (kRowsPerLoad * i >= rows_here) break;   // (uniform)
+      const int rr = kRowsPerLoad * i + (lane_e >> kChunkShift), c = lane_e & (kChunks - 1);
+      const int r2 = row0_wg + wave * kRowsPerWave + rr, tok2 = div_rep(r2);
+      bool ok = r2 < M;
+      if constexpr (kTable) ok = ok && tok2 < nv_wg;
+      const u32x4 x = *reinterpret_cast<const u32x4*>(stage + chunk_at(rr, c));
+      if (ok) *reinterpret_cast<u32x4*>(base + row_at(r2, tok2) * stride + off + 16 * c) = x;
+    }
+  };
   if (a.n_splits > 1 && a.f32_partials) {
-    float* op = static_cast<float*>(a.ws_o) + (split * a.rows_total + orow) * kHD;
+    uint8_t* base = static_cast<uint8_t*>(a.ws_o) + split * a.rows_total * (4 * kHD);
 #pragma unroll
-    for (int db = 0; db < kDB; ++db)
+    for (int half = 0; half < 2; ++half) {   // a row of the stage holds half a float32 row
 #pragma unroll
-      for (int qd = 0; qd < 4; ++qd)
-        *reinterpret_cast<float4*>(op + 32 * db + 8 * qd + 4 * hh) =
-            make_float4(oacc[db][4 * qd] * inv, oacc[db][4 * qd + 1] * inv, oacc[db][4 * qd + 2] * inv, oacc[db][4 * qd + 3] * inv);
+      for (int dl = 0; dl < kDB / 2; ++dl)
+#pragma unroll
+        for (int qd = 0; qd < 4; ++qd) {
+          const f32x16_t& o = oacc[half * (kDB / 2) + dl];
+          *reinterpret_cast<float4*>(stage + chunk_at(n_e, 8 * dl + 2 * qd + hh_e)) =
+              make_float4(o[4 * qd] * inv, o[4 * qd + 1] * inv, o[4 * qd + 2] * inv, o[4 * qd + 3] * inv);
+        }
+      flush_rows(base, 4 * kHD, half * kRowBytes);
+    }
   } else {
-    bf16_t* op = a.n_splits == 1 ? a.out + orow * kHD : static_cast<bf16_t*>(a.ws_o) + (split * a.rows_total + orow) * kHD;
 #pragma unroll
     for (int db = 0; db < kDB; ++db)
 #pragma unroll
       for (int qd = 0; qd < 4; ++qd) {
-        const int d = 32 * db + 8 * qd + 4 * hh;
         uint2 v;
         v.x = pack_bf16x2(oacc[db][4 * qd] * inv, oacc[db][4 * qd + 1] * inv);
         v.y = pack_bf16x2(oacc[db][4 * qd + 2] * inv, oacc[db][4 * qd + 3] * inv);
-        *reinterpret_cast<uint2*>(op + d) = v;
+        *reinterpret_cast<uint2*>(stage + chunk_at(n_e, 4 * db + qd) + 8 * hh_e) = v;
       }
+    if (a.n_splits == 1) flush_rows(reinterpret_cast<uint8_t*>(a.out), kRowBytes, 0);
+    else flush_rows(static_cast<uint8_t*>(a.ws_o) + split * a.rows_total * kRowBytes, kRowBytes, 0);
   }
-  if (a.n_splits > 1 && hh == 0) a.ws_ml[split * a.rows_total + orow] = make_float2(m_run, l_tot);
 }
 
 // Merge the key-range splits of each query row by log-sum-exp.  Split s left its output
