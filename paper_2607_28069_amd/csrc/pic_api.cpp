@@ -117,10 +117,11 @@ bool mfma_decode(const pic_model* m) { return m->dtype == PIC_BF16; }
 
 // The workspace a prefill of n_suffix tokens after max_ctx needs: what the query call says, except
 // for launches that fill half the GPU, which run unsplit without it.
-pic_status check_prefill_workspace(const pic_model* m, int32_t batch, int32_t n_suffix, int32_t max_ctx, size_t ws_bytes) {
+pic_status check_prefill_workspace(const pic_model* m, int32_t batch, int32_t n_suffix, int32_t max_ctx, size_t ws_bytes,
+                                   bool inline_layout = false) {
   if (!mfma_prefill(m)) return PIC_OK;
   const pic::AttnShape s = shape_of(m, batch, max_ctx + n_suffix, 0.f);
-  const size_t need = pic::prefill_bf16_workspace(s, n_suffix, max_ctx);
+  const size_t need = pic::prefill_bf16_workspace(s, n_suffix, max_ctx, inline_layout);
   if (ws_bytes < need && !pic::prefill_bf16_may_run_whole(s, n_suffix))
     return fail(PIC_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", need, ws_bytes);
   return PIC_OK;
@@ -726,7 +727,7 @@ PIC_API size_t pic_frontier_workspace_bytes(const pic_model* model, int32_t batc
   if (check_attn_model(model) != PIC_OK || batch < 0 || n_inline < 0 || max_len < 0) return 0;
   if (!mfma_prefill(model)) return 0;
   const int32_t max_ctx = max_len > n_inline ? max_len - n_inline : 0;
-  return pic::prefill_bf16_workspace(shape_of(model, batch, max_len, 0.f), n_inline, max_ctx);
+  return pic::prefill_bf16_workspace(shape_of(model, batch, max_len, 0.f), n_inline, max_ctx, true);
 }
 
 PIC_API pic_status pic_frontier_prefill_attn(const pic_model* model, const void* q,
@@ -758,7 +759,8 @@ PIC_API pic_status pic_frontier_prefill_attn(const pic_model* model, const void*
   if (!pos) return fail(PIC_ERR_INVALID_ARG, "pos is NULL");
   if (!n_valid) return fail(PIC_ERR_INVALID_ARG, "n_valid is NULL");
   if (workspace == nullptr) ws_bytes = 0;
-  PIC_CHECK(check_prefill_workspace(model, batch, n_inline, max_len > n_inline ? max_len - n_inline : 0, ws_bytes));
+  PIC_CHECK(check_prefill_workspace(model, batch, n_inline, max_len > n_inline ? max_len - n_inline : 0, ws_bytes,
+                                    true));
   const hipStream_t st = (hipStream_t)stream;
   const pic::AttnShape s = shape_of(model, batch, cache_cap, scale);
   pic::RowPos rp;

@@ -121,7 +121,7 @@ struct F32AttnArgs {
 };
 hipError_t launch_attn_f32(const F32AttnArgs& a);
 
-size_t prefill_bf16_workspace(const AttnShape& s, int32_t n_suffix, int32_t max_ctx);
+size_t prefill_bf16_workspace(const AttnShape& s, int32_t n_suffix, int32_t max_ctx, bool inline_layout = false);
 // Launches that may bring less than that: they then run the best plan that fits, or unsplit.
 bool prefill_bf16_may_run_whole(const AttnShape& s, int32_t n_suffix);
 // Also writes k_suf / v_suf into cache slots [ctx_len[b], ctx_len[b] + n_suffix).

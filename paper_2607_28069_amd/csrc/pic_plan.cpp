@@ -59,7 +59,9 @@ int prefill_bf16_splits_held(const AttnShape& s, int32_t n_suffix, int32_t max_c
 // (rows addressed one by one, masked, perhaps turned) and is better one that is not full.  Ties go
 // to fewer splits.  Measured, whole / as planned: 8 requests of 10K keys x 128 tokens (128 units)
 // 225 / 175 us, of 4K 98 / 84; 16 of 4K x 16 tokens 81 / 61; 4 of 32K, 28/4 heads x 256 tokens (112
-// units) 434 us in 9 splits / 420 in 2.  256 units stay whole.
+// units) 434 us in 9 splits / 420 in 2.  256 units stay whole.  (Inline layouts, whose m-tiles differ
+// in length, even themselves out and are planned with ws_bytes 0: 6 requests of 5K keys x 426
+// inline tokens, 336 units, 142 us whole and 160 in splits.)
 SplitPlan plan_prefill_splits(const AttnShape& s, int32_t n_suffix, int32_t max_ctx, size_t ws_bytes) {
   SplitPlan p;
   const int held = prefill_bf16_splits_held(s, n_suffix, max_ctx);
@@ -95,8 +97,8 @@ SplitPlan plan_prefill_splits(const AttnShape& s, int32_t n_suffix, int32_t max_
   return p;
 }
 
-size_t prefill_bf16_workspace(const AttnShape& s, int32_t n_suffix, int32_t max_ctx) {
-  const SplitPlan p = plan_prefill_splits(s, n_suffix, max_ctx, SIZE_MAX);
+size_t prefill_bf16_workspace(const AttnShape& s, int32_t n_suffix, int32_t max_ctx, bool inline_layout) {
+  const SplitPlan p = plan_prefill_splits(s, n_suffix, max_ctx, inline_layout ? 0 : SIZE_MAX);
   return p.n_splits == 1 ? 0 : (size_t)p.n_splits * prefill_rows(s, n_suffix) * prefill_partial_bytes(s.head_dim, p.f32_partials);
 }
 
