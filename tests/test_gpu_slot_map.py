@@ -1,0 +1,52 @@
+"""Slot and tile maps at the sizes where their launch changes: one span, several, the last one partial,
+wide spans, and block lists long enough for the three separate launches; against the host's expansion."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+import paper_2607_28069_amd as pic  # noqa: E402
+
+
+@pytest.mark.parametrize("batch,cap,n_blocks", [(1, 1, 0), (1, 63, 1), (2, 64, 3), (1, 1024, 16), (3, 1025, 60), (2, 5000, 150),
+                                                (40, 8200, 3000),          # 4096-slot spans
+                                                (64, 16384, 40000)])       # the separate launches
+@pytest.mark.parametrize("tiles", [True, False])
+def test_maps(batch, cap, n_blocks, tiles):
+    rng = np.random.default_rng(batch * cap + n_blocks)
+    blocks = np.zeros(max(n_blocks, 1), pic.BLOCK_DTYPE)
+    # aligned runs, shifted ones, gaps, one-token and invalid blocks; no slot covered twice
+    slots = [(b, s) for b in range(batch) for s in range(0, cap, 64)]
+    order = rng.permutation(len(slots))
+    n = 0
+    for j in order[:n_blocks]:
+        b, s = slots[j]
+        k = int(rng.integers(1, 65)) if rng.random() < 0.4 else 64
+        blocks[n] = (b, int(rng.integers(0, 1 << 20)) if rng.random() < 0.5 else 64 * s, s, min(k, cap - s), int(rng.integers(-99, 99)))
+        n += 1
+    while n < n_blocks:   # the rest: out of range, skipped
+        blocks[n] = [(batch, 0, 0, 1, 0), (0, 0, cap, 1, 0), (0, 0, -1, 1, 0), (0, 0, 0, 65, 0), (-1, 0, 0, 64, 0)][n % 5]
+        n += 1
+    src, dl = np.zeros((batch, cap), np.int32), np.zeros((batch, cap), np.int32)
+    for b, t, s, k, d in blocks[:n_blocks].tolist():
+        if 0 <= b < batch and 0 < k <= 64 and s >= 0 and s + k <= cap:
+            src[b, s:s + k] = t + np.arange(k)
+            dl[b, s:s + k] = d
+    nt = pic.pic_slot_map_tiles(cap)
+    want = np.zeros((batch, nt, 2), np.int32)
+    want[:, :, 0] = -1
+    for b in range(batch):
+        for t in range(cap // 64):
+            x, y = src[b, 64 * t:64 * t + 64], dl[b, 64 * t:64 * t + 64]
+            if (x == x[0] + np.arange(64)).all() and (y == y[0]).all():
+                want[b, t] = x[0], y[0]
+    dev = torch.from_numpy(blocks.view(np.int32).copy()).cuda()
+    a, c = (torch.full((batch, cap), 123, dtype=torch.int32, device="cuda") for _ in range(2))
+    tm = torch.full((batch, nt, 2), 123, dtype=torch.int32, device="cuda") if tiles else None
+    pic.pic_build_slot_map(dev, n_blocks, batch, cap, a, c, tm)
+    torch.cuda.synchronize()
+    assert np.array_equal(a.cpu().numpy(), src) and np.array_equal(c.cpu().numpy(), dl)
+    if tiles:
+        assert np.array_equal(tm.cpu().numpy(), want)
