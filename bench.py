@@ -216,7 +216,7 @@ class DeviceWorkload:
         self.table_block = (self.mad + 1) * (D // 2) * 2 if self.model.rope_tables > 1 else 0
         # zero-copy prefill: the context tiles that are not whole pool runs are composed for all
         # layers in one launch after the slot map, and the per-layer calls then take no slot map
-        # (the matrix-core path; the row path turns every key through the slot map)
+        # (head_dim 128; other shapes pass the slot map to every call)
         self.tiles_ahead = w.dtype == "bf16" and w.head_dim == 128
         if w.rope_scaling == "llama3":
             pic.pic_rope_table_init_freq(self.model, pic.pic_rope_llama3_freq(D, w.rope_theta), self.mad,
