@@ -352,6 +352,36 @@ void fuzz_attention() {
   }
 }
 
+// ---- one workspace, sized for the largest call, serves the smaller ones ----
+struct PrefillShape {
+  int32_t batch, n_suf, max_ctx;
+};
+void prefill_workspace_of_the_largest() {
+  struct {
+    int hq, hkv, D;
+    PrefillShape large, small;
+  } cases[] = {
+      {64, 8, 128, {6, 8, 49250}, {1, 8, 49250}},     // fewer requests: more, smaller ranges
+      {32, 8, 128, {5, 191, 1407}, {5, 45, 1407}},    // fewer tokens, the large call unsplit
+      {8, 2, 128, {31, 67, 889}, {31, 47, 889}},
+      {28, 4, 128, {14, 71, 1362}, {14, 6, 1362}},
+      {32, 8, 64, {5, 23, 77348}, {1, 23, 77348}},
+  };
+  for (const auto& c : cases) {
+    pic_model m = model(1, c.hq, c.hkv, c.D, PIC_BF16);
+    Buf ws(pic_prefill_workspace_bytes(&m, c.large.batch, c.large.n_suf, c.large.max_ctx));
+    const PrefillShape& s = c.small;
+    const int32_t cap = s.max_ctx + s.n_suf;
+    const size_t row = (size_t)c.D * 2, toks = (size_t)s.batch * s.n_suf;
+    Buf q(toks * c.hq * row), out(toks * c.hq * row), ks(toks * c.hkv * row), vs(toks * c.hkv * row);
+    Buf ck((size_t)s.batch * c.hkv * cap * row), cv((size_t)s.batch * c.hkv * cap * row);
+    Buf ctx(s.batch * sizeof(int32_t));
+    for (int b = 0; b < s.batch; ++b) ctx.as<int32_t>()[b] = s.max_ctx - b;
+    EXPECT(pic_suffix_prefill_attn(&m, q.p, ks.p, vs.p, ck.p, cv.p, s.batch, cap, ctx.as<int32_t>(), s.max_ctx, s.n_suf,
+                                   0.f, out.p, ws.n ? ws.p : nullptr, ws.n, nullptr) == PIC_OK);
+  }
+}
+
 // ---- argument checks: failures launch nothing ----
 void argument_checks() {
   pic_model m = model(1, 32, 8, 128, PIC_BF16);
@@ -398,6 +428,7 @@ int main(int argc, char** argv) {
     valid_compose();
     fuzz_attention();
   }
+  if (seed == 1) prefill_workspace_of_the_largest();   // (no random draws)
   argument_checks();
   if (failures) {
     std::printf("sanitizer driver: %d failures\n", failures);
