@@ -363,7 +363,9 @@ pic_status pic_frontier_prefill_attn(const pic_model* model, const void* q, cons
      workspace                 pic_decode_workspace_bytes(...) bytes for the same batch,
                                max_base_len + step + 1 and n_splits; 0 bytes (NULL allowed)
                                when the split count is 1.  With n_splits 0, a call of 256 or more
-                               (request, kv head, layer) triples that brings less runs unsplit. */
+                               (request, kv head, layer) triples that brings less runs unsplit, and
+                               below that the query may name more than the count picked needs, so
+                               that one workspace serves smaller batches too. */
 size_t pic_decode_workspace_bytes(const pic_model* model, int32_t batch, int32_t max_len,
                                   int32_t n_splits);
 pic_status pic_decode_attn(const pic_model* model, const void* q, const void* k_new,

@@ -798,8 +798,8 @@ PIC_API size_t pic_decode_workspace_bytes(const pic_model* model, int32_t batch,
                                           int32_t n_splits) {
   if (check_attn_model(model) != PIC_OK || batch < 0 || max_len < 0 || n_splits < 0) return 0;
   if (!mfma_decode(model)) return 0;
-  if (n_splits == 0) n_splits = pic_decode_auto_splits(model, batch, max_len);
-  return pic::decode_bf16_workspace(shape_of(model, batch, max_len, 0.f), max_len, n_splits);
+  const pic::AttnShape s = shape_of(model, batch, max_len, 0.f);
+  return n_splits == 0 ? pic::decode_bf16_auto_workspace(s, max_len) : pic::decode_bf16_workspace(s, max_len, n_splits);
 }
 
 namespace {

@@ -188,6 +188,7 @@ inline int32_t decode_head_groups(const AttnShape& s) { return (s.n_q_heads / s.
 size_t decode_scratch_bytes();
 hipError_t decode_scratch_ptr(void** out);
 size_t decode_bf16_workspace(const AttnShape& s, int32_t max_len, int32_t n_splits);
+size_t decode_bf16_auto_workspace(const AttnShape& s, int32_t max_len);
 // Also writes k_new / v_new into slot base_len[b] + step of the cache.  With rope_table, q and
 // k_new are given unrotated and turned to that position (table block of layer l at
 // rope_table + l * table_stride; positions <= max_abs_delta).

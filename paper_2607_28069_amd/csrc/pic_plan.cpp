@@ -112,6 +112,18 @@ bool prefill_bf16_may_run_whole(const AttnShape& s, int32_t n_suffix) { return p
 
 int32_t slot_map_tiles(int32_t map_cap) { return (int32_t)(((int64_t)map_cap + kPrefillKeys - 1) / kPrefillKeys); }
 
+namespace {
+
+int64_t decode_pairs(const AttnShape& s) { return (int64_t)s.batch * s.n_kv_heads * s.n_layers * decode_head_groups(s); }
+
+// A split count, so that every wave keeps at least kDecodeMinWaveKeys keys.
+int32_t decode_cap_splits(int64_t splits, int32_t max_len) {
+  const int64_t per_split = (int64_t)kDecodeWaves * kDecodeMinWaveKeys;
+  return (int32_t)std::max<int64_t>(1, std::min(splits, ((int64_t)max_len + per_split - 1) / per_split));
+}
+
+}  // namespace
+
 // Key ranges per (request, kv head, group of 16 query heads).  One workgroup alone on a compute
 // unit streams about 36 GB/s, so some 200 of the 256 reach the HBM's rate and what counts is that
 // no compute unit gets one workgroup more than the others:
@@ -124,22 +136,28 @@ int32_t slot_map_tiles(int32_t map_cap) { return (int32_t)(((int64_t)map_cap + k
 //    pairs of 2K keys 71 and 95).  Head_dim 64 keeps four workgroups on a compute unit, which
 //    evens that out by itself (384 pairs: 120 us whole, 137 us in 4).
 int32_t decode_bf16_auto_splits(const AttnShape& s, int32_t max_len) {
-  const int64_t pairs = (int64_t)s.batch * s.n_kv_heads * s.n_layers * decode_head_groups(s);
+  const int64_t pairs = decode_pairs(s);
   if (pairs > 256) {
     const int64_t rounds = (pairs + 255) / 256;
     return s.head_dim == 128 && max_len >= 4096 && rounds * 256 * 10 >= pairs * 13 ? 4 : 1;
   }
-  int64_t splits = pairs > 0 ? 256 / pairs : 1;
-  const int64_t per_split = (int64_t)kDecodeWaves * kDecodeMinWaveKeys;
-  const int64_t max_splits = (max_len + per_split - 1) / per_split;
-  if (splits > max_splits) splits = max_splits;
-  if (splits < 1) splits = 1;
-  return (int32_t)splits;
+  return decode_cap_splits(pairs > 0 ? 256 / pairs : 1, max_len);
 }
 
 // Launches that fill the GPU unsplit: with no split count asked for they run without a workspace.
 bool decode_bf16_may_run_whole(const AttnShape& s) {
-  return (int64_t)s.batch * s.n_kv_heads * s.n_layers * decode_head_groups(s) >= 256;
+  return decode_pairs(s) >= 256;
+}
+
+// Bytes for a call that leaves the split count to the library: at least what that count needs, and up
+// to 256 pairs those of the rounded-up count.  A caller sizes one workspace for its largest batch,
+// and counts rounded down leave too little there for a smaller one (88 pairs in 2 ranges need the
+// room of 176, 64 pairs in 4 that of 256).
+size_t decode_bf16_auto_workspace(const AttnShape& s, int32_t max_len) {
+  int32_t splits = decode_bf16_auto_splits(s, max_len);
+  const int64_t pairs = decode_pairs(s);
+  if (pairs > 0 && pairs <= 256) splits = std::max(splits, decode_cap_splits((256 + pairs - 1) / pairs, max_len));
+  return decode_bf16_workspace(s, max_len, splits);
 }
 
 size_t decode_bf16_workspace(const AttnShape& s, int32_t, int32_t n_splits) {

@@ -382,6 +382,26 @@ void prefill_workspace_of_the_largest() {
   }
 }
 
+void decode_workspace_of_the_largest() {
+  struct {
+    int hq, hkv, D;
+    int32_t large_batch, small_batch, len;
+  } cases[] = {
+      {32, 8, 128, 11, 8, 4096}, {28, 4, 128, 6, 1, 16500}, {8, 2, 128, 34, 32, 3575}, {32, 8, 64, 14, 2, 14540},
+      {64, 8, 128, 3, 2, 20886}, {40, 1, 128, 40, 30, 3000},
+  };
+  for (const auto& c : cases) {
+    pic_model m = model(1, c.hq, c.hkv, c.D, PIC_BF16);
+    Buf ws(pic_decode_workspace_bytes(&m, c.large_batch, c.len, 0));
+    const size_t row = (size_t)c.D * 2, B = c.small_batch;
+    Buf q(B * c.hq * row), out(B * c.hq * row), kn(B * c.hkv * row), vn(B * c.hkv * row);
+    Buf ck(B * c.hkv * c.len * row), cv(B * c.hkv * c.len * row), base(B * sizeof(int32_t));
+    for (size_t b = 0; b < B; ++b) base.as<int32_t>()[b] = c.len - 1 - (int32_t)b;
+    EXPECT(pic_decode_attn(&m, q.p, kn.p, vn.p, ck.p, cv.p, c.small_batch, c.len, base.as<int32_t>(), 0, c.len - 1, 0.f, 0,
+                           out.p, ws.p, ws.n, nullptr) == PIC_OK);
+  }
+}
+
 // ---- argument checks: failures launch nothing ----
 void argument_checks() {
   pic_model m = model(1, 32, 8, 128, PIC_BF16);
@@ -428,7 +448,10 @@ int main(int argc, char** argv) {
     valid_compose();
     fuzz_attention();
   }
-  if (seed == 1) prefill_workspace_of_the_largest();   // (no random draws)
+  if (seed == 1) {   // (no random draws)
+    prefill_workspace_of_the_largest();
+    decode_workspace_of_the_largest();
+  }
   argument_checks();
   if (failures) {
     std::printf("sanitizer driver: %d failures\n", failures);
