@@ -1147,6 +1147,11 @@ prefill_bf16_kernel(PrefillArgs a) {
   const float inv = 1.f / l_tot;
   uint8_t* const stage = (wave & 4 ? (wave & 2 ? v_lds1 : v_lds0) : (wave & 2 ? k_lds1 : k_lds0)) + (wave & 1) * (kTileBytes / 2);
   auto chunk_at = [&](int row, int c) { return row * kRowBytes + ((c ^ k_swz<HD>(row)) << 4); };
+  // (the lanes of the wave read what others wrote: the compiler must keep the two apart)
+  auto wave_sync = []() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
   // rows of kRowBytes bytes from the stage to base + row * stride + off (row: of out, or of a split)
   auto flush_rows = [&](uint8_t* base, int64_t stride, int off) {
     const int rows_here = M - (row0_wg + wave * kRowsPerWave);
@@ -1173,7 +1178,9 @@ prefill_bf16_kernel(PrefillArgs a) {
           *reinterpret_cast<float4*>(stage + chunk_at(n_e, 8 * dl + 2 * qd + hh_e)) =
               make_float4(o[4 * qd] * inv, o[4 * qd + 1] * inv, o[4 * qd + 2] * inv, o[4 * qd + 3] * inv);
         }
+      wave_sync();
       flush_rows(base, 4 * kHD, half * kRowBytes);
+      wave_sync();
     }
   } else {
 #pragma unroll
@@ -1185,6 +1192,7 @@ prefill_bf16_kernel(PrefillArgs a) {
         v.y = pack_bf16x2(oacc[db][4 * qd + 2] * inv, oacc[db][4 * qd + 3] * inv);
         *reinterpret_cast<uint2*>(stage + chunk_at(n_e, 4 * db + qd) + 8 * hh_e) = v;
       }
+    wave_sync();
     if (a.n_splits == 1) flush_rows(reinterpret_cast<uint8_t*>(a.out), kRowBytes, 0);
     else flush_rows(static_cast<uint8_t*>(a.ws_o) + split * a.rows_total * kRowBytes, kRowBytes, 0);
   }
