@@ -363,9 +363,10 @@ pic_status pic_frontier_prefill_attn(const pic_model* model, const void* q, cons
      workspace                 pic_decode_workspace_bytes(...) bytes for the same batch,
                                max_base_len + step + 1 and n_splits; 0 bytes (NULL allowed)
                                when the split count is 1.  With n_splits 0, a call of 256 or more
-                               (request, kv head, layer) triples that brings less runs unsplit, and
-                               below that the query may name more than the count picked needs, so
-                               that one workspace serves smaller batches too. */
+                               units (request x kv head x layer x group of 16 query heads) that
+                               brings less runs unsplit, and below that the query may name more
+                               than the count picked needs, so that one workspace serves smaller
+                               batches too. */
 size_t pic_decode_workspace_bytes(const pic_model* model, int32_t batch, int32_t max_len,
                                   int32_t n_splits);
 pic_status pic_decode_attn(const pic_model* model, const void* q, const void* k_new,
@@ -396,11 +397,12 @@ pic_status pic_decode_attn_rope(const pic_model* model, const void* q, const voi
    instead of a caller workspace.  Allocates and frees nothing; the first call on a device looks
    the array up (hipGetSymbolAddress) with that device current.
    Same arguments, checks and results as pic_decode_attn (bit-identical outputs for the same
-   n_splits).  PIC_ERR_WORKSPACE when the split partials,
-   pic_decode_workspace_bytes(model, batch, max_base_len + step + 1, n_splits), exceed
-   PIC_DECODE_SCRATCH_BYTES.  Every call on one GPU shares that GPU's array: calls that overlap
-   on one GPU (other streams, other threads) race and must be ordered by the caller.  Nothing in
-   the array needs clearing: each split launch writes every partial it combines. */
+   n_splits; with n_splits 0, a call of 256 or more units (see 4) runs unsplit and touches no
+   scratch, as pic_decode_attn does that brings no workspace).  PIC_ERR_WORKSPACE when the partials
+   of the split count taken exceed PIC_DECODE_SCRATCH_BYTES.  Every call on one GPU shares that
+   GPU's array: calls that overlap on one GPU (other streams, other threads) race and must be
+   ordered by the caller.  Nothing in the array needs clearing: each split launch writes every
+   partial it combines. */
 #define PIC_DECODE_SCRATCH_BYTES ((size_t)8 << 20)
 pic_status pic_decode_attn_noalloc(const pic_model* model, const void* q, const void* k_new,
                                    const void* v_new, void* cache_k, void* cache_v, int32_t batch,
@@ -412,7 +414,7 @@ pic_status pic_decode_attn_noalloc(const pic_model* model, const void* q, const 
 const char* pic_status_string(pic_status status);
 /* Thread-local description of the last failure on this thread ("" if none). */
 const char* pic_last_error(void);
-/* Split count pic_decode_attn picks for n_splits = 0 (host only). */
+/* Split count pic_decode_attn picks for n_splits = 0 with the workspace the query names (host only). */
 int32_t pic_decode_auto_splits(const pic_model* model, int32_t batch, int32_t max_len);
 
 #ifdef __cplusplus

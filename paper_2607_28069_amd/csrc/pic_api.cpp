@@ -850,8 +850,9 @@ pic_status decode_impl(const pic_model* model, const void* q, const void* k_new,
     return launch_f32(s, q, k_new, v_new, cache_k, cache_v, pos, 1, out, st, "decode attention launch");
   }
   if (n_splits == 0) {
+    // (a launch that fills the GPU whole leaves the scratch array alone: such calls may overlap)
     n_splits = pic::decode_bf16_auto_splits(s, (int32_t)max_len);
-    const size_t held = use_scratch ? pic::decode_scratch_bytes() : (workspace ? ws_bytes : 0);
+    const size_t held = use_scratch || !workspace ? 0 : ws_bytes;
     if (pic::decode_bf16_workspace(s, (int32_t)max_len, n_splits) > held && pic::decode_bf16_may_run_whole(s))
       n_splits = 1;
   }

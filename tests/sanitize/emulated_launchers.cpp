@@ -18,6 +18,7 @@ namespace pic {
 namespace emu {
 
 long launches = 0;   // kernel launches the emulation has run (test driver reads it)
+long scratch_lookups = 0;   // times a launch asked for the allocation-free decode's array
 
 namespace {
 
@@ -593,6 +594,7 @@ hipError_t launch_decode_bf16(const AttnShape& s, const bf16_t* q, const bf16_t*
 // The allocation-free decode's per-GPU array: host memory of the same size here.
 size_t decode_scratch_bytes() { return PIC_DECODE_SCRATCH_BYTES; }
 hipError_t decode_scratch_ptr(void** out) {
+  ++emu::scratch_lookups;
   static void* buf = std::malloc(PIC_DECODE_SCRATCH_BYTES);
   *out = buf;
   return buf ? hipSuccess : hipErrorOutOfMemory;

@@ -24,6 +24,7 @@
 namespace pic {
 namespace emu {
 extern long launches;
+extern long scratch_lookups;
 }
 }  // namespace pic
 
@@ -402,6 +403,25 @@ void decode_workspace_of_the_largest() {
   }
 }
 
+// ---- the allocation-free decode leaves its shared array alone where the launch fills the GPU ----
+void scratch_of_full_launches() {
+  struct {
+    int hq, hkv;
+    int32_t batch, len;
+    bool full;
+  } cases[] = {{8, 8, 33, 4100, true}, {16, 8, 48, 6200, true}, {8, 8, 66, 4100, true}, {8, 8, 12, 4100, false}};
+  for (const auto& c : cases) {
+    pic_model m = model(1, c.hq, c.hkv, 128, PIC_BF16);
+    const size_t row = 256, B = c.batch;
+    Buf q(B * c.hq * row), out(B * c.hq * row), kn(B * c.hkv * row), vn(B * c.hkv * row);
+    Buf ck(B * c.hkv * c.len * row), cv(B * c.hkv * c.len * row), base(B * sizeof(int32_t));
+    const long before = pic::emu::scratch_lookups;
+    EXPECT(pic_decode_attn_noalloc(&m, q.p, kn.p, vn.p, ck.p, cv.p, c.batch, c.len, base.as<int32_t>(), 0, c.len - 1, 0.f,
+                                   0, out.p, nullptr) == PIC_OK);
+    EXPECT((pic::emu::scratch_lookups == before) == c.full);
+  }
+}
+
 // ---- argument checks: failures launch nothing ----
 void argument_checks() {
   pic_model m = model(1, 32, 8, 128, PIC_BF16);
@@ -451,6 +471,7 @@ int main(int argc, char** argv) {
   if (seed == 1) {   // (no random draws)
     prefill_workspace_of_the_largest();
     decode_workspace_of_the_largest();
+    scratch_of_full_launches();
   }
   argument_checks();
   if (failures) {

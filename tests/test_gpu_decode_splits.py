@@ -83,3 +83,19 @@ def test_a_batch_that_fills_the_gpu_needs_no_workspace(batch):
                                     max(base), x["out"])
         torch.cuda.synchronize()
         _check(x, base, 0)
+
+
+def test_noalloc_full_launch_equals_the_call_without_a_workspace():
+    base = [4200 - 17 * b for b in range(33)]
+    outs = []
+    for noalloc in (False, True):
+        x = _inputs(16, 8, 128, base, 0)
+        if noalloc:
+            pic.pic_decode_attn_noalloc(x["model"], x["q"], x["k"], x["v"], x["K"], x["V"], 33, x["cap"], x["base"], 0,
+                                        max(base), x["out"])
+            torch.cuda.synchronize()
+        else:
+            _decode(x, base, 0, 0, ws=None)
+        _check(x, base, 0)
+        outs.append(x["out"])
+    assert torch.equal(outs[0], outs[1])
