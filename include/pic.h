@@ -236,7 +236,8 @@ pic_status pic_compose_shared(const pic_model* model, const void* pool_k, const 
      scale                    softmax scale; 0 means 1/sqrt(head_dim)
      workspace                pic_prefill_workspace_bytes(...) bytes (may be 0 bytes); a call that
                               fills half the GPU (128 or more units of 256 packed query rows)
-                              and brings less runs with fewer or no key-range splits
+                              and brings less, or one that is not 16-byte aligned, runs with
+                              fewer or no key-range splits
    The prefill kernels (this call and 3a-3c) address one cache stream [cache_cap][D], one
    request's suffix rows [n_suffix][Hkv][D] and one pool head [pool_tokens][D] with 32-bit byte
    offsets: each of cache_cap, n_suffix * Hkv and pool_tokens must be below 2^24
@@ -364,9 +365,9 @@ pic_status pic_frontier_prefill_attn(const pic_model* model, const void* q, cons
                                max_base_len + step + 1 and n_splits; 0 bytes (NULL allowed)
                                when the split count is 1.  With n_splits 0, a call of 256 or more
                                units (request x kv head x layer x group of 16 query heads) that
-                               brings less runs unsplit, and below that the query may name more
-                               than the count picked needs, so that one workspace serves smaller
-                               batches too. */
+                               brings less (or one that is not 16-byte aligned) runs unsplit, and
+                               below that the query may name more than the count picked needs, so
+                               that one workspace serves smaller batches too. */
 size_t pic_decode_workspace_bytes(const pic_model* model, int32_t batch, int32_t max_len,
                                   int32_t n_splits);
 pic_status pic_decode_attn(const pic_model* model, const void* q, const void* k_new,

@@ -115,16 +115,21 @@ pic_status check_attn_model(const pic_model* m) { return check_model(m); }
 bool mfma_prefill(const pic_model* m) { return m->dtype == PIC_BF16; }
 bool mfma_decode(const pic_model* m) { return m->dtype == PIC_BF16; }
 
-// The workspace a prefill of n_suffix tokens after max_ctx needs: what the query call says, except
-// for launches that fill half the GPU, which run unsplit without it.
-pic_status check_prefill_workspace(const pic_model* m, int32_t batch, int32_t n_suffix, int32_t max_ctx, size_t ws_bytes,
-                                   bool inline_layout = false) {
+// The workspace of a prefill of n_suffix tokens after max_ctx: what the query call says.  A launch
+// that fills half the GPU can do without and runs whole then; a workspace that is not aligned
+// counts as not brought there (it is not needed), and is refused where it is needed.
+pic_status check_prefill_workspace(const pic_model* m, int32_t batch, int32_t n_suffix, int32_t max_ctx,
+                                   const void* workspace, size_t* ws_bytes, bool inline_layout = false) {
   if (!mfma_prefill(m)) return PIC_OK;
   const pic::AttnShape s = shape_of(m, batch, max_ctx + n_suffix, 0.f);
+  if (workspace == nullptr) *ws_bytes = 0;
+  if (pic::prefill_bf16_may_run_whole(s, n_suffix)) {
+    if (!aligned16(workspace)) *ws_bytes = 0;
+    return PIC_OK;
+  }
   const size_t need = pic::prefill_bf16_workspace(s, n_suffix, max_ctx, inline_layout);
-  if (ws_bytes < need && !pic::prefill_bf16_may_run_whole(s, n_suffix))
-    return fail(PIC_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", need, ws_bytes);
-  return PIC_OK;
+  if (*ws_bytes < need) return fail(PIC_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", need, *ws_bytes);
+  return need > 0 ? check_ptr(workspace, "workspace") : PIC_OK;
 }
 
 // Attention over a float32 cache: n_q query rows per request at the positions `pos` gives them.
@@ -530,8 +535,7 @@ PIC_API pic_status pic_suffix_prefill_attn(const pic_model* model, const void* q
   PIC_CHECK(check_ptr(cache_v, "cache_v"));
   PIC_CHECK(check_ptr(out, "out"));
   if (!ctx_len) return fail(PIC_ERR_INVALID_ARG, "ctx_len is NULL");
-  if (workspace == nullptr) ws_bytes = 0;
-  PIC_CHECK(check_prefill_workspace(model, batch, n_suffix, max_ctx, ws_bytes));
+  PIC_CHECK(check_prefill_workspace(model, batch, n_suffix, max_ctx, workspace, &ws_bytes));
   const hipStream_t st = (hipStream_t)stream;
   const pic::AttnShape s = shape_of(model, batch, cache_cap, scale);
   // a4: both kernels store the suffix K/V into slots [ctx, ctx + n_suffix) (App. C.1: inline
@@ -589,8 +593,7 @@ PIC_API pic_status pic_suffix_prefill_attn_rope(const pic_model* model, const vo
   PIC_CHECK(check_ptr(table, "table"));
   PIC_CHECK(check_ptr(out, "out"));
   if (!ctx_len) return fail(PIC_ERR_INVALID_ARG, "ctx_len is NULL");
-  if (workspace == nullptr) ws_bytes = 0;
-  PIC_CHECK(check_prefill_workspace(model, batch, n_suffix, max_ctx, ws_bytes));
+  PIC_CHECK(check_prefill_workspace(model, batch, n_suffix, max_ctx, workspace, &ws_bytes));
   const pic::AttnShape s = shape_of(model, batch, cache_cap, scale);
   const int64_t stride = n_tables(model) > 1 ? (int64_t)(max_abs_delta + 1) * (model->head_dim / 2) : 0;
   return hip_status(pic::launch_prefill_bf16_rope(
@@ -705,8 +708,7 @@ PIC_API pic_status pic_paged_prefill_attn(const pic_model* model, const void* po
   // call reads whole runs from the pool and every other tile from the cache
   if (!slot_src && !tile_map) return fail(PIC_ERR_INVALID_ARG, "slot map is NULL (allowed only with a tile map)");
   if (!ctx_len) return fail(PIC_ERR_INVALID_ARG, "ctx_len is NULL");
-  if (workspace == nullptr) ws_bytes = 0;
-  PIC_CHECK(check_prefill_workspace(model, batch, n_suffix, max_ctx, ws_bytes));
+  PIC_CHECK(check_prefill_workspace(model, batch, n_suffix, max_ctx, workspace, &ws_bytes));
   const pic::AttnShape s = shape_of(model, batch, cache_cap, scale);
   const int64_t stride = n_tables(model) > 1 ? (int64_t)(max_abs_delta + 1) * (model->head_dim / 2) : 0;
   return hip_status(pic::launch_prefill_bf16_paged(
@@ -758,9 +760,8 @@ PIC_API pic_status pic_frontier_prefill_attn(const pic_model* model, const void*
   PIC_CHECK(check_ptr(out, "out"));
   if (!pos) return fail(PIC_ERR_INVALID_ARG, "pos is NULL");
   if (!n_valid) return fail(PIC_ERR_INVALID_ARG, "n_valid is NULL");
-  if (workspace == nullptr) ws_bytes = 0;
-  PIC_CHECK(check_prefill_workspace(model, batch, n_inline, max_len > n_inline ? max_len - n_inline : 0, ws_bytes,
-                                    true));
+  PIC_CHECK(check_prefill_workspace(model, batch, n_inline, max_len > n_inline ? max_len - n_inline : 0, workspace,
+                                    &ws_bytes, true));
   const hipStream_t st = (hipStream_t)stream;
   const pic::AttnShape s = shape_of(model, batch, cache_cap, scale);
   pic::RowPos rp;
@@ -852,7 +853,7 @@ pic_status decode_impl(const pic_model* model, const void* q, const void* k_new,
   if (n_splits == 0) {
     // (a launch that fills the GPU whole leaves the scratch array alone: such calls may overlap)
     n_splits = pic::decode_bf16_auto_splits(s, (int32_t)max_len);
-    const size_t held = use_scratch || !workspace ? 0 : ws_bytes;
+    const size_t held = use_scratch || !workspace || !aligned16(workspace) ? 0 : ws_bytes;
     if (pic::decode_bf16_workspace(s, (int32_t)max_len, n_splits) > held && pic::decode_bf16_may_run_whole(s))
       n_splits = 1;
   }

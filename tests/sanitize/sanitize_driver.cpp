@@ -422,6 +422,42 @@ void scratch_of_full_launches() {
   }
 }
 
+// ---- workspaces a launch can do without: full, short, misaligned, missing ----
+void optional_workspaces() {
+  pic_model m = model(1, 32, 8, 128, PIC_BF16);
+  const size_t row = 256;
+  const int32_t B = 33, n = 128, max_ctx = 4100, cap = max_ctx + n, pre = 8;   // 128 units of prefill, 264 pairs of decode
+  Buf q((size_t)pre * n * 32 * row), out((size_t)pre * n * 32 * row), ks((size_t)pre * n * 8 * row), vs((size_t)pre * n * 8 * row);
+  Buf ck((size_t)B * 8 * cap * row), cv((size_t)B * 8 * cap * row), len(B * sizeof(int32_t));
+  for (int b = 0; b < B; ++b) len.as<int32_t>()[b] = max_ctx - 500 * (b % 8);
+  const size_t ws_need = pic_prefill_workspace_bytes(&m, pre, n, max_ctx), dws_need = pic_decode_workspace_bytes(&m, B, max_ctx + 1, 0);
+  EXPECT(ws_need > 0 && dws_need > 0);
+  Buf ws(ws_need + 8), dws(dws_need + 8);
+  struct {
+    size_t off, less;
+    bool split;
+  } forms[] = {{0, 0, true}, {0, 1, false}, {8, 0, false}, {0, SIZE_MAX, false}};
+  for (const auto& f : forms) {   // (a split launch is followed by its combine)
+    const bool none = f.less == SIZE_MAX;
+    long before = pic::emu::launches;
+    EXPECT(pic_suffix_prefill_attn(&m, q.p, ks.p, vs.p, ck.p, cv.p, pre, cap, len.as<int32_t>(), max_ctx, n, 0.f, out.p,
+                                   none ? nullptr : ws.as<char>() + f.off, none ? 0 : ws_need - f.less, nullptr) == PIC_OK);
+    EXPECT(pic::emu::launches - before == (f.split ? 2 : 1));
+    before = pic::emu::launches;
+    EXPECT(pic_decode_attn(&m, q.p, ks.p, vs.p, ck.p, cv.p, B, cap, len.as<int32_t>(), 0, max_ctx, 0.f, 0, out.p,
+                           none ? nullptr : dws.as<char>() + f.off, none ? 0 : dws_need - f.less, nullptr) == PIC_OK);
+    EXPECT(pic::emu::launches - before == (f.split ? 2 : 1));
+  }
+  // where it is needed it has to be there, whole and aligned
+  Buf need(pic_prefill_workspace_bytes(&m, 1, n, max_ctx) + 8);
+  const long before = pic::emu::launches;
+  EXPECT(pic_suffix_prefill_attn(&m, q.p, ks.p, vs.p, ck.p, cv.p, 1, cap, len.as<int32_t>(), max_ctx, n, 0.f, out.p,
+                                 need.as<char>() + 8, need.n - 8, nullptr) == PIC_ERR_MISALIGNED);
+  EXPECT(pic_suffix_prefill_attn(&m, q.p, ks.p, vs.p, ck.p, cv.p, 1, cap, len.as<int32_t>(), max_ctx, n, 0.f, out.p,
+                                 need.p, need.n - 9, nullptr) == PIC_ERR_WORKSPACE);
+  EXPECT(pic::emu::launches == before);
+}
+
 // ---- argument checks: failures launch nothing ----
 void argument_checks() {
   pic_model m = model(1, 32, 8, 128, PIC_BF16);
@@ -472,6 +508,7 @@ int main(int argc, char** argv) {
     prefill_workspace_of_the_largest();
     decode_workspace_of_the_largest();
     scratch_of_full_launches();
+    optional_workspaces();
   }
   argument_checks();
   if (failures) {
