@@ -30,6 +30,8 @@
 //  * A tile some rows see only in part has its scores masked; a probability of 0 times a value
 //    that is not finite is no 0, so a tile that holds such a value takes its PV products one
 //    query column at a time, with the values that column does not see cleared.
+#include <algorithm>
+
 #include "pic_bounds.h"
 #include "pic_internal.h"
 
@@ -59,9 +61,10 @@ __device__ __forceinline__ float column_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// grid (ceil(m_tiles * batch * Hkv / 8) * 8, L), 64 W threads; NB blocks of 16 query rows
+// grid (ceil(n_units / 8) * 8, L), 64 W threads; NB blocks of 16 query rows.  Units [unit0, unit0 +
+// n_units) of the m_tiles * batch * Hkv.
 template <int HD, int NB, int W>
-__global__ void __launch_bounds__(64 * W) attn_f32_kernel(F32AttnArgs a, int32_t m_tiles, int32_t n_units) {
+__global__ void __launch_bounds__(64 * W) attn_f32_kernel(F32AttnArgs a, int32_t m_tiles, int32_t unit0, int32_t n_units) {
   constexpr int QJ = HD / 16;         // 16-byte pieces of a Q or K row per lane
   constexpr int VH = HD / 64;         // 16-byte pieces of a V row per lane
   constexpr int ROWS = 16 * NB;
@@ -72,8 +75,9 @@ __global__ void __launch_bounds__(64 * W) attn_f32_kernel(F32AttnArgs a, int32_t
   // blocks are dealt round-robin to the 8 XCDs: a contiguous range of units for each, so that
   // the m-tiles of one (request, kv head) read its keys through one L2
   const int per_xcd = (n_units + kNumXcd - 1) / kNumXcd;
-  const int unit = ((int)blockIdx.x % kNumXcd) * per_xcd + (int)blockIdx.x / kNumXcd;
-  if (unit >= n_units) return;
+  const int at = ((int)blockIdx.x % kNumXcd) * per_xcd + (int)blockIdx.x / kNumXcd;
+  if (at >= n_units) return;
+  const int unit = unit0 + at;
   const AttnShape& s = a.s;
   const int mt = m_tiles - 1 - unit % m_tiles, bg = unit / m_tiles;   // later rows see more keys: first
   const int Hkv = s.n_kv_heads, Hq = s.n_q_heads, n_rep = Hq / Hkv, n_q = a.n_q;
@@ -339,12 +343,17 @@ template <int HD, int NB, int W>
 hipError_t launch_as(const F32AttnArgs& a) {
   const int64_t M = (int64_t)a.n_q * (a.s.n_q_heads / a.s.n_kv_heads);
   const int64_t m_tiles = (M + 16 * NB - 1) / (16 * NB);
-  const int64_t units = m_tiles * a.s.batch * a.s.n_kv_heads;
-  const int64_t grid = (units + kNumXcd - 1) / kNumXcd * kNumXcd;
-  if (grid > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((attn_f32_kernel<HD, NB, W>), dim3((unsigned)grid, a.s.n_layers), dim3(64 * W), 0, a.stream, a,
-                     (int32_t)m_tiles, (int32_t)units);
-  return hipGetLastError();
+  const int64_t units = m_tiles * a.s.batch * a.s.n_kv_heads;   // at most the query rows: fits int32
+  // a grid holds fewer than 2^32 threads per dimension: 2^23 workgroups of 512
+  constexpr int64_t kPart = int64_t(1) << 22;
+  for (int64_t u0 = 0; u0 < units; u0 += kPart) {
+    const int64_t part = std::min(units - u0, kPart), grid = (part + kNumXcd - 1) / kNumXcd * kNumXcd;
+    hipLaunchKernelGGL((attn_f32_kernel<HD, NB, W>), dim3((unsigned)grid, a.s.n_layers), dim3(64 * W), 0, a.stream, a,
+                       (int32_t)m_tiles, (int32_t)u0, (int32_t)part);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace
