@@ -26,6 +26,7 @@
 //  * rope variant: q and k_new arrive unrotated and are turned to position p (the delta-angle
 //    table's row p) in registers -- the query once, the new key in the tile that holds it and
 //    where it is stored -- with the float32 arithmetic of the re-rotation kernel.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -494,7 +495,8 @@ decode_bf16_kernel(DecodeArgs a) {
   }
 }
 
-// grid (B * Hq, L), 256 threads: merge the ranges of one query head by log-sum-exp.  HD / 4 lanes
+// grid (rows, L), 256 threads, rows [row0, row0 + grid) of the B * Hq: merge the ranges of one query
+// head by log-sum-exp.  HD / 4 lanes
 // hold 4 head dims each of one range, 1024 / HD ranges side by side, and every range's loads are
 // issued before any is used; the range groups then merge in LDS.  (One wave walking the ranges
 // took 4.9 us for 8 or 32 of them: a memory round trip per 8, once for the maxima and once for
@@ -505,11 +507,11 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(const float* __rest
                                                              const int32_t* __restrict__ base_len, int32_t batch,
                                                              int32_t n_q_heads, int32_t max_base, int32_t step,
                                                              int32_t cache_cap, int32_t n_splits, int32_t chunk,
-                                                             bf16_t* __restrict__ out) {
+                                                             int32_t row0, bf16_t* __restrict__ out) {
   constexpr int kLanes = HD / 4, kGroups = 256 / kLanes, kBatch = 4;
   __shared__ float m_s[kGroups], l_s[kGroups];
   __shared__ __attribute__((aligned(16))) float o_s[kGroups * HD];
-  const int b = blockIdx.x / n_q_heads, h = blockIdx.x - b * n_q_heads, l = blockIdx.y;
+  const int bh = row0 + blockIdx.x, b = bh / n_q_heads, h = bh - b * n_q_heads, l = blockIdx.y;
   const SplitPlace place = place_of(deal_splits(base_len, batch, max_base, step, cache_cap, n_splits, chunk), b);
   if (place.n == 1) return;   // (uniform) a whole request: its output is stored
   const int64_t slot0 = ((int64_t)l * batch * n_splits + place.first) * n_q_heads + (int64_t)h * place.n;
@@ -570,10 +572,15 @@ hipError_t launch_decode_hd(const DecodeArgs& a, dim3 grid, bool rope, bool inte
     hipLaunchKernelGGL((decode_bf16_kernel<HD, true, false>), grid, dim3(256), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || n_splits == 1) return e;
-  hipLaunchKernelGGL(decode_combine_kernel<HD>, dim3(s.batch * s.n_q_heads, s.n_layers), dim3(256), 0, stream,
-                     a.ws_o, a.ws_ml, a.base_len, s.batch, s.n_q_heads, a.max_base, a.step, a.cache_cap, n_splits,
-                     a.chunk, a.out);
-  return hipGetLastError();
+  // (a grid holds fewer than 2^32 threads per dimension)
+  const int64_t rows = (int64_t)s.batch * s.n_q_heads, kPart = int64_t(1) << 23;
+  for (int64_t row0 = 0; row0 < rows && e == hipSuccess; row0 += kPart) {
+    hipLaunchKernelGGL(decode_combine_kernel<HD>, dim3((unsigned)std::min(rows - row0, kPart), s.n_layers), dim3(256), 0,
+                       stream, a.ws_o, a.ws_ml, a.base_len, s.batch, s.n_q_heads, a.max_base, a.step, a.cache_cap,
+                       n_splits, a.chunk, (int32_t)row0, a.out);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 }  // namespace
