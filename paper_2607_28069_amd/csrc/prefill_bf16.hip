@@ -1317,7 +1317,8 @@ __global__ void __launch_bounds__(256) map_spans_kernel(const pic_block* __restr
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
       const int i = i0 + 256 * u;
-      if (i >= n_blocks || req[u] != b || dst[u] >= s0 + kSpan || dst[u] <= s0 - PIC_BLOCK_TOKENS) continue;
+      const int64_t off = (int64_t)dst[u] - s0;   // (s0 + kSpan may pass 2^31)
+      if (i >= n_blocks || req[u] != b || off >= kSpan || off <= -PIC_BLOCK_TOKENS) continue;
       const int at = atomicAdd(&n_found, 1);
       if (at < kList) {
         found[at] = i;

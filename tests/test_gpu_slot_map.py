@@ -50,3 +50,23 @@ def test_maps(batch, cap, n_blocks, tiles):
     assert np.array_equal(a.cpu().numpy(), src) and np.array_equal(c.cpu().numpy(), dl)
     if tiles:
         assert np.array_equal(tm.cpu().numpy(), want)
+
+
+def test_the_largest_map():
+    """map_cap of 2^31 - 1 slots: blocks at both ends and in the last 4096 slots."""
+    cap = 2 ** 31 - 1
+    rows = [(0, 5, 0, 64, 7), (0, 100, cap - 64, 64, -9), (0, 300, cap - 4000, 50, 3), (0, 400, 2 ** 30, 64, 1)]
+    blocks = torch.tensor(rows, dtype=torch.int32, device="cuda")
+    src, dl = (torch.full((cap,), -5, dtype=torch.int32, device="cuda") for _ in range(2))
+    tiles = torch.full((2 ** 25, 2), -5, dtype=torch.int32, device="cuda")
+    pic.pic_build_slot_map(blocks, len(rows), 1, cap, src, dl, tiles)
+    torch.cuda.synchronize()
+    for _, s, d, n, shift in rows:
+        assert torch.equal(src[d:d + n], torch.arange(s, s + n, dtype=torch.int32, device="cuda"))
+        assert bool((dl[d:d + n] == shift).all())
+    covered = sum(n for _, _, _, n, _ in rows)
+    # (counted in pieces: a mask of the whole map at once would be another 2 GB)
+    assert sum(int(torch.count_nonzero(p)) for p in dl.split(1 << 28)) == covered
+    whole = torch.nonzero(tiles[:, 0] >= 0).flatten().tolist()
+    assert whole == [0, 2 ** 24]
+    assert tiles[0].tolist() == [5, 7] and tiles[2 ** 24].tolist() == [400, 1] and tiles[-1].tolist() == [-1, 0]
