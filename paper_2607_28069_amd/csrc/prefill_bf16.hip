@@ -1280,30 +1280,37 @@ __global__ void __launch_bounds__(256) prefill_combine_kernel(const PT* __restri
 
 namespace {
 
+constexpr int kSpan = 1024;   // slots per workgroup of map_spans_kernel
+
 // Slot and tile map in one launch, for maps and block lists of ordinary size: grid (batch * spans),
 // 256 threads.  A workgroup owns kSpan slots of one request: it looks through the block list for
 // blocks that reach them, expands those into LDS and writes its part of the maps from there.  It
 // saves two of the clear, expand and tile launches below (2 to 5 us each), but reads the list once
-// per span, so long lists stay with them.  Zero-copy calls with their map: 2 requests of 950 slots
-// 37.4 -> 34.4 us, 5 of 930 (two layers) 64.9 -> 63.8, 2 of 33K (four layers) unchanged.
-template <int kSpan>
+// per span, so long lists stay with them.  Map with tile map, three launches / this one, us: 1
+// request of 16K slots 13.7 / 5.2, 16 of them (256 spans, 4096 blocks) 13.7 / 6.0, 32 (512, 8192)
+// 13.5 / 9.2; past those limits 48 (768, 12288) 13.9 / 15.1, 64 (1024, 16384) 15.7 / 22.5.  Spans of
+// 4096 slots were no better there (17 requests 13.1, 90 requests 25.4 against 19.5).  A block of few
+// tokens is expanded by the thread that finds it: with a wave for each, 4096 one-token blocks in 4
+// spans took 23 us instead of 6.
 __global__ void __launch_bounds__(256) map_spans_kernel(const pic_block* __restrict__ blocks, int32_t n_blocks,
                                                         int32_t batch, int32_t map_cap, int32_t spans,
                                                         int32_t* smap, int32_t* dmap, int32_t* tmap,
                                                         int32_t map_tiles) {
   static_assert(kSpan % kKeys == 0, "whole tiles");
-  constexpr int kList = 512, kAhead = 8;   // blocks kept for expansion; list entries loaded together
+  // blocks kept for expansion, list entries loaded together, tokens of a block its finder expands
+  constexpr int kList = 256, kAhead = 8, kShort = 8;
   __shared__ int32_t src[kSpan], del[kSpan];
-  __shared__ int32_t found[kList], n_found;
+  __shared__ int4 found[kList];            // (first slot in the span, source, tokens, shift)
+  __shared__ int32_t n_found;
   const int b = blockIdx.x / spans, s0 = (blockIdx.x - b * spans) * kSpan;
   if (threadIdx.x == 0) n_found = 0;
   for (int i = threadIdx.x; i < kSpan; i += 256) src[i] = del[i] = 0;
   __syncthreads();
-  auto expand = [&](const pic_block& blk, int t) {   // token t of a block
-    const int p = blk.dst_slot + t - s0;
+  auto expand = [&](const int4& f, int t) {   // token t of a block
+    const int p = f.x + t;
     if (p >= 0 && p < kSpan) {
-      src[p] = blk.src_token + t;
-      del[p] = blk.delta;
+      src[p] = f.y + t;
+      del[p] = f.w;
     }
   };
   for (int i0 = threadIdx.x; i0 < n_blocks; i0 += 256 * kAhead) {
@@ -1317,22 +1324,23 @@ __global__ void __launch_bounds__(256) map_spans_kernel(const pic_block* __restr
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
       const int i = i0 + 256 * u;
-      const int64_t off = (int64_t)dst[u] - s0;   // (s0 + kSpan may pass 2^31)
+      const int64_t off = (int64_t)dst[u] - s0;
       if (i >= n_blocks || req[u] != b || off >= kSpan || off <= -PIC_BLOCK_TOKENS) continue;
-      const int at = atomicAdd(&n_found, 1);
+      const pic_block blk = blocks[i];
+      if (!map_block_ok(blk, batch, map_cap)) continue;
+      const int4 f = make_int4((int)off, blk.src_token, blk.n_tokens, blk.delta);
+      const int at = f.z > kShort ? atomicAdd(&n_found, 1) : kList;
       if (at < kList) {
-        found[at] = i;
-      } else {   // (a list of very short blocks)
-        const pic_block blk = blocks[i];
-        if (map_block_ok(blk, batch, map_cap))
-          for (int t = 0; t < blk.n_tokens; ++t) expand(blk, t);
+        found[at] = f;
+      } else {   // (or blocks that overlap, more than a span has room for)
+        for (int t = 0; t < f.z; ++t) expand(f, t);
       }
     }
   }
   __syncthreads();
-  for (int f = threadIdx.x >> 6; f < min(n_found, kList); f += 4) {   // one wave per block, a token per lane
-    const pic_block blk = blocks[found[f]];
-    if (map_block_ok(blk, batch, map_cap) && (int)(threadIdx.x & 63) < blk.n_tokens) expand(blk, threadIdx.x & 63);
+  for (int i = threadIdx.x >> 6; i < min(n_found, kList); i += 4) {   // one wave per block, a token per lane
+    const int4 f = found[i];
+    if ((int)(threadIdx.x & 63) < f.z) expand(f, threadIdx.x & 63);
   }
   __syncthreads();
   const int n_here = min(kSpan, map_cap - s0);
@@ -1553,19 +1561,10 @@ hipError_t launch_slot_map(const pic_block* blocks, int32_t n_blocks, int32_t ba
                            int32_t* smap, int32_t* dmap, int32_t* tmap, hipStream_t stream) {
   const int64_t n_map = (int64_t)batch * map_cap;
   if (n_map == 0) return hipSuccess;
-  // 1024 slots per workgroup, or 4096 where that gives more than one workgroup per compute unit;
-  // the three launches where the list would be read through for more than 2^23 blocks in all
-  // (64 requests of 16K slots in 16384 blocks: 5.2 million)
-  const bool wide = (int64_t)batch * (((int64_t)map_cap + 1023) / 1024) > 256;
-  const int32_t spans = wide ? (int32_t)(((int64_t)map_cap + 4095) / 4096) : (int32_t)(((int64_t)map_cap + 1023) / 1024);
-  if ((int64_t)batch * spans * (n_blocks > 0 ? n_blocks : 1) <= (int64_t(1) << 23)) {
-    const dim3 grid((unsigned)((int64_t)batch * spans));
-    if (wide)
-      hipLaunchKernelGGL(map_spans_kernel<4096>, grid, dim3(256), 0, stream, blocks, n_blocks, batch, map_cap, spans,
-                         smap, dmap, tmap, slot_map_tiles(map_cap));
-    else
-      hipLaunchKernelGGL(map_spans_kernel<1024>, grid, dim3(256), 0, stream, blocks, n_blocks, batch, map_cap, spans,
-                         smap, dmap, tmap, slot_map_tiles(map_cap));
+  const int64_t spans = ((int64_t)map_cap + kSpan - 1) / kSpan;
+  if (batch * spans <= 512 && n_blocks <= 8192) {
+    hipLaunchKernelGGL(map_spans_kernel, dim3((unsigned)(batch * spans)), dim3(256), 0, stream, blocks, n_blocks, batch,
+                       map_cap, (int32_t)spans, smap, dmap, tmap, slot_map_tiles(map_cap));
     return hipGetLastError();
   }
   int64_t g = (n_map + 255) / 256;
