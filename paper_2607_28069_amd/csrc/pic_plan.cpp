@@ -124,24 +124,32 @@ int32_t decode_cap_splits(int64_t splits, int32_t max_len) {
 
 }  // namespace
 
-// Key ranges per (request, kv head, group of 16 query heads).  One workgroup alone on a compute
-// unit streams about 36 GB/s, so some 200 of the 256 reach the HBM's rate and what counts is that
-// no compute unit gets one workgroup more than the others:
-//  * up to 128 pairs, as many ranges as leave at most one workgroup per compute unit, each wave
-//    keeping at least kDecodeMinWaveKeys keys (a second one on a few units costs as much as on all:
-//    192 pairs of 10K keys took 150 us in 1 range and 168 us in 2, 160 pairs of 8K 104 and 117);
+// Key ranges per (request, kv head, group of 16 query heads), each wave keeping at least
+// kDecodeMinWaveKeys keys.  Head_dim 128: one workgroup alone on a compute unit streams about 36
+// GB/s, so some 200 of the 256 reach the HBM's rate and what counts is that no compute unit gets one
+// workgroup more than the others:
+//  * up to 128 pairs, as many ranges as leave at most one workgroup per compute unit (a second one on
+//    a few units costs as much as on all; rounded down / up, 16K keys: 72 pairs 88 / 124 us, 104 135 /
+//    174, 136 207 / 251, 192 238 / 268, 248 305 / 309; 2K keys: 19 / 21, 25 / 30, 36 / 39, 36 / 41, 47 / 49);
 //  * from 129 to 256, none;
 //  * beyond, none if the last round of 256 is nearly full or the ranges would be short, else 4
 //    (264 pairs of 8K keys: 241 us whole, 191 us in 4; 320: 235 and 197; 384: 264 and 253; but 480
-//    pairs of 2K keys 71 and 95).  Head_dim 64 keeps four workgroups on a compute unit, which
-//    evens that out by itself (384 pairs: 120 us whole, 137 us in 4).
+//    pairs of 2K keys 71 and 95).
+// Head_dim 64 keeps up to four workgroups on a compute unit, which evens that out by itself (384
+// pairs: 120 us whole, 137 us in 4), and each has half the bytes in flight: there the count is rounded
+// up where rounding down leaves under 200 workgroups or one range (down / up, 4K keys, and 16K keys
+// half as long at the shortest: 88 pairs 24.7 / 23.6 and 72 / 69 us, 136 41.9 / 35.1 and 131 / 101, 192
+// 41.1 / 39.7 and 131 / 111, 224 45.2 / 43.3 and 134 / 122), and down elsewhere (72 pairs 18.6 / 19.4
+// and 51 / 56, 104 27.0 / 26.6 and 74 / 74, 120 27.5 / 28.0 and 76 / 78).
 int32_t decode_bf16_auto_splits(const AttnShape& s, int32_t max_len) {
   const int64_t pairs = decode_pairs(s);
   if (pairs > 256) {
     const int64_t rounds = (pairs + 255) / 256;
     return s.head_dim == 128 && max_len >= 4096 && rounds * 256 * 10 >= pairs * 13 ? 4 : 1;
   }
-  return decode_cap_splits(pairs > 0 ? 256 / pairs : 1, max_len);
+  int64_t splits = pairs > 0 ? 256 / pairs : 1;
+  if (s.head_dim == 64 && pairs > 0 && pairs < 256 && (splits == 1 || splits * pairs < 200)) ++splits;
+  return decode_cap_splits(splits, max_len);
 }
 
 // Launches that fill the GPU unsplit: with no split count asked for they run without a workspace.

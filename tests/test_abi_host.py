@@ -473,3 +473,15 @@ def test_noalloc_decode_argument_checks(lib):
     assert need > pic.PIC_DECODE_SCRATCH_BYTES
     assert nd(batch=64, splits=64) == -3
     assert "allocation-free" in pic.pic_last_error()
+
+
+@pytest.mark.parametrize("head_dim,pairs,splits", [
+    (128, 72, 3), (128, 88, 2), (128, 104, 2), (128, 136, 1), (128, 192, 1), (128, 248, 1), (128, 256, 1),
+    (64, 72, 3), (64, 88, 3), (64, 104, 2), (64, 120, 2), (64, 128, 2), (64, 136, 2), (64, 192, 2), (64, 248, 2), (64, 256, 1),
+    (64, 384, 1),
+])
+def test_decode_split_counts(lib, head_dim, pairs, splits):
+    m = _model(head_dim=head_dim, n_layers=1, n_q_heads=32, n_kv_heads=8)
+    assert pic.pic_decode_auto_splits(m, pairs // 8, 16384) == splits
+    need = pic.pic_decode_workspace_bytes(m, pairs // 8, 16384, 0)
+    assert need >= (0 if splits == 1 else pairs * 4 * splits * (head_dim + 2) * 4)
