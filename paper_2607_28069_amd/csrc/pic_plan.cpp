@@ -132,9 +132,11 @@ int32_t decode_cap_splits(int64_t splits, int32_t max_len) {
 //    a few units costs as much as on all; rounded down / up, 16K keys: 72 pairs 88 / 124 us, 104 135 /
 //    174, 136 207 / 251, 192 238 / 268, 248 305 / 309; 2K keys: 19 / 21, 25 / 30, 36 / 39, 36 / 41, 47 / 49);
 //  * from 129 to 256, none;
-//  * beyond, none if the last round of 256 is nearly full or the ranges would be short, else 4
-//    (264 pairs of 8K keys: 241 us whole, 191 us in 4; 320: 235 and 197; 384: 264 and 253; but 480
-//    pairs of 2K keys 71 and 95).
+//  * from 257 to 384, 4 of long enough ranges, equal contexts or not (whole / in 4, 10K keys, and 10K
+//    of uneven length: 264 pairs 306 / 229 us and 235 / 191, 320 313 / 254 and 274 / 205, 384 325 / 304
+//    and 286 / 245; of 4K keys 264 129 / 101 and 97 / 98, 384 139 / 135 and 127 / 134, hence the later line);
+//  * beyond, none: uneven contexts even out by themselves (400 pairs of 4K keys 139 / 144, 520 205 / 185
+//    but uneven 138 / 166, 776 281 / 267 but uneven 209 / 238).
 // Head_dim 64 keeps up to four workgroups on a compute unit, which evens that out by itself (384
 // pairs: 120 us whole, 137 us in 4), and each has half the bytes in flight: there the count is rounded
 // up where rounding down leaves under 200 workgroups or one range (down / up, 4K keys, and 16K keys
@@ -144,8 +146,7 @@ int32_t decode_cap_splits(int64_t splits, int32_t max_len) {
 int32_t decode_bf16_auto_splits(const AttnShape& s, int32_t max_len) {
   const int64_t pairs = decode_pairs(s);
   if (pairs > 256) {
-    const int64_t rounds = (pairs + 255) / 256;
-    return s.head_dim == 128 && max_len >= 4096 && rounds * 256 * 10 >= pairs * 13 ? 4 : 1;
+    return s.head_dim == 128 && pairs <= 384 && max_len >= (pairs <= 352 ? 4096 : 6144) ? 4 : 1;
   }
   int64_t splits = pairs > 0 ? 256 / pairs : 1;
   if (s.head_dim == 64 && pairs > 0 && pairs < 256 && (splits == 1 || splits * pairs < 200)) ++splits;

@@ -485,3 +485,12 @@ def test_decode_split_counts(lib, head_dim, pairs, splits):
     assert pic.pic_decode_auto_splits(m, pairs // 8, 16384) == splits
     need = pic.pic_decode_workspace_bytes(m, pairs // 8, 16384, 0)
     assert need >= (0 if splits == 1 else pairs * 4 * splits * (head_dim + 2) * 4)
+
+
+@pytest.mark.parametrize("pairs,length,splits", [
+    (264, 4095, 1), (264, 4096, 4), (352, 4096, 4), (360, 4096, 1), (360, 6144, 4), (384, 16384, 4), (392, 16384, 1),
+    (520, 16384, 1), (776, 16384, 1),
+])
+def test_decode_split_counts_past_one_round(lib, pairs, length, splits):
+    m = _model(n_layers=1, n_q_heads=32, n_kv_heads=8)
+    assert pic.pic_decode_auto_splits(m, pairs // 8, length) == splits
