@@ -234,10 +234,13 @@ pic_status pic_compose_shared(const pic_model* model, const void* pool_k, const 
      ctx_len [device, batch]  composed lengths; entries are clamped to [0, max_ctx]
      max_ctx [host]           bound on ctx_len; max_ctx + n_suffix <= cache_cap
      scale                    softmax scale; 0 means 1/sqrt(head_dim)
-     workspace                pic_prefill_workspace_bytes(...) bytes (may be 0 bytes); a call that
-                              fills half the GPU (128 or more units of 256 packed query rows)
-                              and brings less, or one that is not 16-byte aligned, runs with
-                              fewer or no key-range splits
+     workspace                pic_prefill_workspace_bytes(...) bytes (may be 0 bytes).  Calls of 128
+                              or more units (256 packed query rows of one request, kv head and
+                              layer) can do without: those that bring less, or a workspace that is
+                              not 16-byte aligned, run in one key range.  Above 192 units the
+                              query says 0; below, it is a few float32 (under 128 units bfloat16)
+                              outputs per query row and head: 8 requests x 128 tokens, 32 heads of
+                              128: 34 MB; at most some 100 MB at 32K keys, 150 MB at 128K.
    The prefill kernels (this call and 3a-3c) address one cache stream [cache_cap][D], one
    request's suffix rows [n_suffix][Hkv][D] and one pool head [pool_tokens][D] with 32-bit byte
    offsets: each of cache_cap, n_suffix * Hkv and pool_tokens must be below 2^24

@@ -53,27 +53,33 @@ int prefill_bf16_splits_held(const AttnShape& s, int32_t n_suffix, int32_t max_c
 // Key-range splits of the prefill, by estimated time in us.  Under load the chip sits at its power
 // limit, where a busy compute unit runs slower the more of them are busy: a workgroup's 64-key
 // tile takes t_few with up to half of them busy and t_full with all (measured: 16 to 128
-// workgroups 1.35 us, 192 1.65, 256 2.0; up to 128 rows the loads bound it, 1.15 us; at head_dim
-// 64 1.0 and 1.2 us).  A split run adds the combine launch (5 us, a little more for each split) and
-// the partials, written and read at ~5 TB/s; the split that ends in the suffix has dearer tiles
-// (rows addressed one by one, masked, perhaps turned) and is better one that is not full.  Ties go
-// to fewer splits.  Measured, whole / as planned: 8 requests of 10K keys x 128 tokens (128 units)
-// 225 / 175 us, of 4K 98 / 84; 16 of 4K x 16 tokens 81 / 61; 4 of 32K, 28/4 heads x 256 tokens (112
-// units) 434 us in 9 splits / 420 in 2.  256 units stay whole.  (Inline layouts, whose m-tiles differ
-// in length, even themselves out and are planned with ws_bytes 0: 6 requests of 5K keys x 426
-// inline tokens, 336 units, 142 us whole and 160 in splits.)
+// workgroups 1.35 us, 192 1.65, 256 2.0; up to 128 rows the loads bound it, 1.15 to 1.2 us in short
+// ranges, 1.55 where all are busy for long; at head_dim 64 1.0 and 1.2 us).  A split run adds the
+// combine launch (5 us, a little more for each split) and the partials, written and read at ~5
+// TB/s; the split that ends in the suffix has dearer tiles (rows addressed one by one, masked,
+// perhaps turned) and is better one that is not full.  Ties go to fewer splits.
+//  * Below 128 units up to the held count: 4 requests of 32K, 28/4 heads x 256 tokens (112 units) 434 us
+//    in 9 splits / 420 in 2.
+//  * From 128 to 192, where the plan's full workspace is there and the estimate promises 2.5 %, else
+//    whole.  Whole / split, us: 8 requests of 10K x 128 tokens (128 units) 222 / 173, 16 of 4K x 32
+//    76 / 61, 10 of 10K x 128 (160 units) 245 / 227, 12 of 32K x 128 (192) 828 / 772; contexts down to
+//    half as long: 225 / 160, 64 / 50, 230 / 209.
+//  * Beyond, none: up to 256 there is little to gain (28 requests of 32K x 32 tokens, 224 units: 701 us
+//    whole, 772 in 8), and past a full round, where equal contexts would gain, rounds are not in lockstep:
+//    uneven contexts fill the last one by themselves (40 requests of 2K to 4K keys, 28/4 heads x 73
+//    tokens, 320 units: 165 us whole, 196 in 2; 48 of 5K to 10K x 32 tokens, 384 units: 345 / 379).
 SplitPlan plan_prefill_splits(const AttnShape& s, int32_t n_suffix, int32_t max_ctx, size_t ws_bytes) {
   SplitPlan p;
   const int held = prefill_bf16_splits_held(s, n_suffix, max_ctx);
   const int64_t base = prefill_units(s, n_suffix);
+  const bool may_whole = prefill_bf16_may_run_whole(s, n_suffix);
   p.m_tiles = (int)prefill_m_tiles(s, n_suffix);
   p.f32_partials = held == 1;
   const double split_bytes = (double)prefill_rows(s, n_suffix) * (double)prefill_partial_bytes(s.head_dim, p.f32_partials);
-  const double room = held > 1 ? held * split_bytes : (base >= 128 ? (double)ws_bytes : 0.0);
   const int tiles = prefill_tiles(n_suffix, max_ctx);
   const bool narrow = (int64_t)n_suffix * (s.n_q_heads / s.n_kv_heads) <= 128;
   const double t_few = s.head_dim == 64 ? 1.0 : (narrow ? 1.15 : 1.36);
-  const double t_full = s.head_dim == 64 || narrow ? 1.2 : 2.0;
+  const double t_full = s.head_dim == 64 ? 1.2 : (narrow ? (may_whole ? 1.55 : 1.2) : 2.0);
   auto tile_us = [&](int64_t active) { return active <= 128 ? t_few : t_few + (t_full - t_few) * (double)(active - 128) / 128.0; };
   auto range = [&](int sp) { return (tiles + sp - 1) / sp; };
   auto cost = [&](int sp) {
@@ -81,15 +87,17 @@ SplitPlan plan_prefill_splits(const AttnShape& s, int32_t n_suffix, int32_t max_
     const double us = range(sp) * ((double)(wgs / 256) * t_full + (wgs % 256 ? tile_us(wgs % 256) : 0.0));
     return sp == 1 ? us : us + 5.0 + 0.3 * sp + 2.0 * sp * split_bytes / 5e6 + (sp * range(sp) == tiles ? 1.0 : 0.0);
   };
+  const int most = !may_whole ? held : (base <= 192 ? kPrefillMaxSplits : 1);
   int best = 1;
   double best_us = cost(1);
-  for (int sp = 2; sp <= kPrefillMaxSplits && sp * split_bytes <= room; ++sp) {
+  for (int sp = 2; sp <= most; ++sp) {
     if ((tiles + range(sp) - 1) / range(sp) < sp) continue;   // (the same ranges as fewer splits)
     if (cost(sp) < best_us * 0.99) {
       best = sp;
       best_us = cost(sp);
     }
   }
+  if (may_whole && (best_us > cost(1) * 0.975 || best * split_bytes > (double)ws_bytes)) best = 1;
   // (short launches: what the estimate cannot tell apart, machines of other clocks do)
   if (held > 1 && best_us < 100.0 && cost(held) < best_us + 2.0) best = held;
   p.n_splits = best;

@@ -494,3 +494,16 @@ def test_decode_split_counts(lib, head_dim, pairs, splits):
 def test_decode_split_counts_past_one_round(lib, pairs, length, splits):
     m = _model(n_layers=1, n_q_heads=32, n_kv_heads=8)
     assert pic.pic_decode_auto_splits(m, pairs // 8, length) == splits
+
+
+# units of 256 query rows: 128 (split where its workspace is there), 192, and above, where launches run whole
+@pytest.mark.parametrize("n_q_heads,n_kv_heads,head_dim,batch,n_suffix,max_ctx,splits", [
+    (32, 8, 128, 8, 128, 10240, 2), (32, 8, 128, 12, 128, 32768, 4), (32, 8, 64, 10, 128, 10240, 3),
+    (32, 8, 128, 13, 128, 32768, 0), (32, 8, 128, 28, 32, 32768, 0), (32, 8, 128, 16, 128, 10368, 0),
+    (32, 8, 128, 17, 128, 32768, 0), (32, 8, 128, 20, 128, 10240, 0), (32, 8, 64, 33, 32, 32768, 0),
+    (28, 4, 128, 40, 73, 4096, 0), (32, 8, 128, 12, 256, 10240, 0), (32, 8, 128, 128, 256, 10240, 0),
+])
+def test_prefill_workspace_of_launches_that_can_run_whole(lib, n_q_heads, n_kv_heads, head_dim, batch, n_suffix, max_ctx, splits):
+    m = _model(n_layers=1, n_q_heads=n_q_heads, n_kv_heads=n_kv_heads, head_dim=head_dim)
+    need = pic.pic_prefill_workspace_bytes(m, batch, n_suffix, max_ctx)
+    assert need == splits * batch * n_suffix * n_q_heads * (4 * head_dim + 8)
