@@ -260,7 +260,8 @@ pic_status pic_suffix_prefill_attn(const pic_model* model, const void* q, const 
    per-layer tables, layer l's frequencies) as it loads them, in the float32 arithmetic and bf16
    rounding of pic_rerotate_keys, and stores the turned keys into the cache.  The result is
    bit-identical to turning q and k_suf with pic_rerotate_keys first and then calling
-   pic_suffix_prefill_attn.  bf16 only.
+   pic_suffix_prefill_attn with the same workspace (see there: from 128 units on a call without
+   one runs in one key range, whose sums round elsewhere).  bf16 only.
      table, max_abs_delta   a pic_rope_table_init table with max_abs_delta >= max_ctx + n_suffix - 1
    (other arguments and the workspace as for pic_suffix_prefill_attn) */
 pic_status pic_suffix_prefill_attn_rope(const pic_model* model, const void* q, const void* k_suf,
@@ -282,7 +283,8 @@ pic_status pic_suffix_prefill_attn_rope(const pic_model* model, const void* q, c
    computes, without writing the composed cache: attention reads the documents' K/V straight
    from the pool through the slot map.
    * tile_map NULL: every key is turned by its shift on load, with the float32 arithmetic and
-     bf16 rounding of pic_compose, so outputs are bit-identical to compose + prefill.
+     bf16 rounding of pic_compose, so outputs are bit-identical to compose + prefill with the
+     same workspace.
    * tile_map from pic_build_slot_map (same blocks, batch and map_cap): a context tile that is
      one pool run under one shift is loaded in one piece, unturned, and the queries are turned
      by -shift for its scores instead (<R(-d) q, k> = <q, R(d) k>: RoPE's relative property
@@ -344,7 +346,10 @@ pic_status pic_paged_prefill_attn(const pic_model* model, const void* pool_k, co
                     are neither stored nor computed (their out rows are left untouched)
      max_len [host] bound on every request's length; max_len <= cache_cap
      scale          softmax scale; 0 means 1/sqrt(head_dim)
-     workspace      pic_frontier_workspace_bytes(...) bytes (may be 0 bytes)
+     workspace      pic_frontier_workspace_bytes(...) bytes: as for pic_suffix_prefill_attn with
+                    n_inline tokens after max_len - n_inline.  On the plain layout (the inline
+                    tokens last) the outputs are that call's bit for bit, if both bring the
+                    workspace the query names or neither does.
    Results assume each request's positions increase with i (as the planner gives them). */
 size_t pic_frontier_workspace_bytes(const pic_model* model, int32_t batch, int32_t n_inline,
                                     int32_t max_len);

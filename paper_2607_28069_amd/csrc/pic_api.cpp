@@ -119,7 +119,7 @@ bool mfma_decode(const pic_model* m) { return m->dtype == PIC_BF16; }
 // that fills half the GPU can do without and runs whole then; a workspace that is not aligned
 // counts as not brought there (it is not needed), and is refused where it is needed.
 pic_status check_prefill_workspace(const pic_model* m, int32_t batch, int32_t n_suffix, int32_t max_ctx,
-                                   const void* workspace, size_t* ws_bytes, bool inline_layout = false) {
+                                   const void* workspace, size_t* ws_bytes) {
   if (!mfma_prefill(m)) return PIC_OK;
   const pic::AttnShape s = shape_of(m, batch, max_ctx + n_suffix, 0.f);
   if (workspace == nullptr) *ws_bytes = 0;
@@ -127,7 +127,7 @@ pic_status check_prefill_workspace(const pic_model* m, int32_t batch, int32_t n_
     if (!aligned16(workspace)) *ws_bytes = 0;
     return PIC_OK;
   }
-  const size_t need = pic::prefill_bf16_workspace(s, n_suffix, max_ctx, inline_layout);
+  const size_t need = pic::prefill_bf16_workspace(s, n_suffix, max_ctx);
   if (*ws_bytes < need) return fail(PIC_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", need, *ws_bytes);
   return need > 0 ? check_ptr(workspace, "workspace") : PIC_OK;
 }
@@ -729,7 +729,7 @@ PIC_API size_t pic_frontier_workspace_bytes(const pic_model* model, int32_t batc
   if (check_attn_model(model) != PIC_OK || batch < 0 || n_inline < 0 || max_len < 0) return 0;
   if (!mfma_prefill(model)) return 0;
   const int32_t max_ctx = max_len > n_inline ? max_len - n_inline : 0;
-  return pic::prefill_bf16_workspace(shape_of(model, batch, max_len, 0.f), n_inline, max_ctx, true);
+  return pic::prefill_bf16_workspace(shape_of(model, batch, max_len, 0.f), n_inline, max_ctx);
 }
 
 PIC_API pic_status pic_frontier_prefill_attn(const pic_model* model, const void* q,
@@ -761,7 +761,7 @@ PIC_API pic_status pic_frontier_prefill_attn(const pic_model* model, const void*
   if (!pos) return fail(PIC_ERR_INVALID_ARG, "pos is NULL");
   if (!n_valid) return fail(PIC_ERR_INVALID_ARG, "n_valid is NULL");
   PIC_CHECK(check_prefill_workspace(model, batch, n_inline, max_len > n_inline ? max_len - n_inline : 0, workspace,
-                                    &ws_bytes, true));
+                                    &ws_bytes));
   const hipStream_t st = (hipStream_t)stream;
   const pic::AttnShape s = shape_of(model, batch, cache_cap, scale);
   pic::RowPos rp;

@@ -93,11 +93,12 @@ constexpr int kDecodeMinWaveKeys = 64;     // fewest keys a decode wave is given
 
 // Key-range split of a prefill launch: m-tiles of query rows, splits per (m-tile, request,
 // kv head), key tiles per split, and whether the splits leave their outputs in float32 (else
-// bf16).  The best plan whose partials fit in ws_bytes.
+// bf16).
 struct SplitPlan {
   int m_tiles, n_splits, tiles_per_split;
   bool f32_partials;
 };
+// (ws_bytes: what a launch that can run whole brings; the others bring what the query says)
 SplitPlan plan_prefill_splits(const AttnShape& s, int32_t n_suffix, int32_t max_ctx, size_t ws_bytes);
 // Bytes of partials per split and query row: the split's output and its (max, sum).
 inline size_t prefill_partial_bytes(int head_dim, bool f32) { return (size_t)head_dim * (f32 ? 4 : 2) + 2 * sizeof(float); }
@@ -121,8 +122,8 @@ struct F32AttnArgs {
 };
 hipError_t launch_attn_f32(const F32AttnArgs& a);
 
-size_t prefill_bf16_workspace(const AttnShape& s, int32_t n_suffix, int32_t max_ctx, bool inline_layout = false);
-// Launches that may bring less than that: they then run the best plan that fits, or unsplit.
+size_t prefill_bf16_workspace(const AttnShape& s, int32_t n_suffix, int32_t max_ctx);
+// Launches that may bring less than that: they then run unsplit.
 bool prefill_bf16_may_run_whole(const AttnShape& s, int32_t n_suffix);
 // Also writes k_suf / v_suf into cache slots [ctx_len[b], ctx_len[b] + n_suffix).
 hipError_t launch_prefill_bf16(const AttnShape& s, const bf16_t* q, const bf16_t* k_suf,

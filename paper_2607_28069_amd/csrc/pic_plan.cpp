@@ -109,9 +109,9 @@ SplitPlan plan_prefill_splits(const AttnShape& s, int32_t n_suffix, int32_t max_
 // the plan takes: a caller sizes one workspace for its largest call, and planned room can be less
 // there than for a smaller one (64 query heads over 8, 8 tokens over 49K keys: 6 requests run in 5
 // ranges of 0.8 MB, one request in 31 of 0.135 MB).
-size_t prefill_bf16_workspace(const AttnShape& s, int32_t n_suffix, int32_t max_ctx, bool inline_layout) {
+size_t prefill_bf16_workspace(const AttnShape& s, int32_t n_suffix, int32_t max_ctx) {
   const int held = prefill_bf16_splits_held(s, n_suffix, max_ctx);
-  const SplitPlan p = plan_prefill_splits(s, n_suffix, max_ctx, inline_layout ? 0 : SIZE_MAX);
+  const SplitPlan p = plan_prefill_splits(s, n_suffix, max_ctx, SIZE_MAX);
   const int n = held > 1 ? held : p.n_splits;
   return n == 1 ? 0 : (size_t)n * prefill_rows(s, n_suffix) * prefill_partial_bytes(s.head_dim, p.f32_partials);
 }

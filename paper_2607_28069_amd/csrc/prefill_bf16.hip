@@ -1464,7 +1464,7 @@ hipError_t launch(const AttnShape& s, PrefillArgs a, int mode, bool interleaved,
   const int n_rep = s.n_q_heads / s.n_kv_heads;
   const int64_t M = (int64_t)n_q * n_rep;
   if (M == 0 || s.batch == 0 || s.n_layers == 0) return hipSuccess;
-  const SplitPlan p = plan_prefill_splits(s, n_q, max_ctx, workspace && mode != kModeTable ? ws_bytes : 0);
+  const SplitPlan p = plan_prefill_splits(s, n_q, max_ctx, workspace ? ws_bytes : 0);
   a.n_suffix = n_q;
   a.n_rep = n_rep;
   a.rep_magic = ((uint64_t(1) << 32) + n_rep - 1) / n_rep;

@@ -224,7 +224,7 @@ hipError_t prefill_walk(const AttnShape& s, const PrefillEmu& a, int mode, int32
   const int n_rep = s.n_q_heads / s.n_kv_heads;
   const int64_t M = (int64_t)n_q * n_rep;
   if (M == 0 || s.batch == 0 || s.n_layers == 0) return hipSuccess;
-  const SplitPlan p = plan_prefill_splits(s, n_q, max_ctx, workspace && mode != kModeTable ? ws_bytes : 0);
+  const SplitPlan p = plan_prefill_splits(s, n_q, max_ctx, workspace ? ws_bytes : 0);
   if (M >= (int64_t(1) << 27)) return hipErrorInvalidValue;
   if (p.n_splits > kPrefillMaxSplits) return hipErrorInvalidValue;
   ++emu::launches;
