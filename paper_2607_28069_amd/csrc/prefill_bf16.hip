@@ -1478,16 +1478,22 @@ hipError_t launch(const AttnShape& s, PrefillArgs a, int mode, bool interleaved,
   a.tiles_per_split = p.tiles_per_split;
   a.n_wg = p.m_tiles * p.n_splits * s.batch * s.n_kv_heads;
   // Inline layouts: m-tiles differ in length (the first sees a prefix, the last everything), and a
-  // launch ended with the last pairs' long m-tiles alone on the chip.  Up to three rounds (96
-  // workgroups on an XCD's 32 compute units) all pairs go m-tile by m-tile, longest first; longer
-  // launches keep the order that shares an L2 up to the last round of pairs.  Measured, pair by
-  // pair / as here / all m-tile by m-tile: 8 requests, 28/4 heads, 576 inline tokens over 10.5K
-  // (64 workgroups per XCD) 487 / 362 / 362 us; 16, 32/8 heads, 256 over 2.9K (64) 160 / 105 / 105;
-  // 16, 576 over 10.8K (144) 878 / 831 / 876.
+  // launch ended with the last pairs' long m-tiles alone on the chip.  Short launches go m-tile by
+  // m-tile, longest first, in all pairs; longer ones keep the order that shares an L2 up to their
+  // last pairs.  Where the lines lie depends on the m-tiles: two or three differ little, and where
+  // they do not differ at all (the inline tokens last) the order only loses the shared L2.
+  // Speed against pair by pair, inline layouts / tokens last, by workgroups per XCD (32 compute
+  // units), everything m-tile by m-tile and only the last 32 or 64 workgroups:
+  //   2 m-tiles   48: 1.09 / 1.00    62: 1.05 / 0.96, last 32 1.02 / 1.01   96: 1.03 / 0.96, 1.02 / 1.01
+  //   3           48: 1.23 / 1.00    78: 1.08 / 0.98, last 32 1.08 / 1.02   96: 1.05 / 0.95, 1.10 / 1.02
+  //   4           60: 1.15 / 1.01    80: 1.24 / 1.01, last 64 1.24 / 1.01   96: 1.12 / 0.98, 1.10 / 1.00
+  //   8           48: 1.24 / 1.04    80: 1.20 / 1.03, last 64 1.22 / 1.03  144: last 64 1.06 / 1.01
+  // (pairs that the XCDs do not share evenly keep the plain order: an XCD's range then starts and ends
+  // inside a pair)
   const int32_t pairs = s.batch * s.n_kv_heads;
   if (mode == kModeTable && p.n_splits == 1 && p.m_tiles > 1 && pairs % kNumXcd == 0) {
-    const int32_t per_xcd = pairs / kNumXcd;
-    a.tail_bgs = (int64_t)per_xcd * p.m_tiles <= 96 ? per_xcd : std::min(per_xcd, (32 + p.m_tiles - 1) / p.m_tiles);
+    const int32_t per_xcd = pairs / kNumXcd, last = p.m_tiles < 4 ? 32 : 64;
+    a.tail_bgs = (int64_t)per_xcd * p.m_tiles <= last + 16 ? per_xcd : std::min(per_xcd, (last + p.m_tiles - 1) / p.m_tiles);
   }
   a.rows_total = (int64_t)s.n_layers * s.batch * n_q * s.n_q_heads;
   a.ws_o = workspace;

@@ -160,3 +160,10 @@ def test_frontier_dispatch_orders_cover_every_row(batch, hq, hkv, d, n):
             ref = torch.softmax(s, -1) @ V[b, h].double()
             got = out[b, :c, h * rep:(h + 1) * rep].reshape(c * rep, d).double()
             assert bool(((got - ref).abs() <= 2e-2 + 1e-2 * ref.abs()).all()), (b, h)
+
+
+# two and three m-tiles, past the line where only the last pairs go m-tile by m-tile (62 and 96 units
+# per XCD), and four at the line (80) and past it (96)
+@pytest.mark.parametrize("batch,hq,hkv,d,n", [(31, 64, 8, 128, 57), (32, 32, 8, 128, 190), (20, 32, 8, 64, 250), (24, 32, 8, 128, 250)])
+def test_frontier_dispatch_orders_of_few_m_tiles(batch, hq, hkv, d, n):
+    test_frontier_dispatch_orders_cover_every_row(batch, hq, hkv, d, n)
