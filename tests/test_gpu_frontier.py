@@ -167,3 +167,9 @@ def test_frontier_dispatch_orders_cover_every_row(batch, hq, hkv, d, n):
 @pytest.mark.parametrize("batch,hq,hkv,d,n", [(31, 64, 8, 128, 57), (32, 32, 8, 128, 190), (20, 32, 8, 64, 250), (24, 32, 8, 128, 250)])
 def test_frontier_dispatch_orders_of_few_m_tiles(batch, hq, hkv, d, n):
     test_frontier_dispatch_orders_cover_every_row(batch, hq, hkv, d, n)
+
+
+# up to 64 rows per (request, kv head) are stored from the registers, more go through LDS
+@pytest.mark.parametrize("batch,hq,hkv,d,n", [(4, 8, 2, 128, 16), (4, 8, 2, 64, 16), (4, 8, 2, 128, 17), (5, 4, 2, 128, 32)])
+def test_frontier_of_few_rows(batch, hq, hkv, d, n):
+    test_frontier_dispatch_orders_cover_every_row(batch, hq, hkv, d, n)
