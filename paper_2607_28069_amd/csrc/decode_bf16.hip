@@ -114,8 +114,7 @@ __device__ __forceinline__ int32_t ceil_div24(int32_t u, int32_t c, float inv) {
   return q + (r > 0 ? 1 : 0) + (r > c ? 1 : 0) - (r <= -c ? 1 : 0);
 }
 __device__ __forceinline__ SplitDeal deal_splits(const int32_t* base_len, int32_t batch, int32_t max_base, int32_t step,
-                                                 int32_t cache_cap, int32_t n_splits, int32_t chunk) {
-  if (!decode_dealt(n_splits, batch, max_base + step + 1)) return {chunk, n_splits, 0, 0};
+                                                 int32_t cache_cap, int32_t n_splits) {
   const int lane = threadIdx.x & 63;
   int32_t u = 0, base = 0;
   if (lane < batch) {
@@ -201,8 +200,9 @@ __device__ __forceinline__ void rot_operand(u32x4 (&c)[Dims<HD>::kSteps], const 
   }
 }
 
-// grid (S * B * Hkv, L), 256 threads
-template <int HD, bool kRope, bool kInterleaved>
+// grid (S * B * Hkv, L), 256 threads.  kDealt: ranges dealt by length (decode_dealt), else n_splits equal
+// ones (a kernel of its own: tested in the kernel, the choice cost launches of 1600 short contexts 1 %).
+template <int HD, bool kRope, bool kInterleaved, bool kDealt>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 decode_bf16_kernel(DecodeArgs a) {
   constexpr int kHD = HD, kRowBytes = Dims<HD>::kRowBytes, kVTileBytes = Dims<HD>::kVTileBytes;
@@ -215,11 +215,10 @@ decode_bf16_kernel(DecodeArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hgrp = blockIdx.x % a.head_groups;           // query heads 16 hgrp .. of kv head g
   const int at = blockIdx.x / a.head_groups;             // [request][kv head][range]
-  const bool dealt = decode_dealt(a.n_splits, a.batch, a.max_base + a.step + 1);
   int b, g, split, chunk = a.chunk;
   int32_t base;
   SplitPlace place;
-  if (!dealt) {
+  if constexpr (!kDealt) {
     split = at % a.n_splits;
     const int bg = at / a.n_splits;
     b = bg / a.n_kv_heads;
@@ -227,7 +226,7 @@ decode_bf16_kernel(DecodeArgs a) {
     place = {a.n_splits, b * a.n_splits};
     base = clamp_len(a.base_len[b], a.max_base);
   } else {
-    const SplitDeal deal = deal_splits(a.base_len, a.batch, a.max_base, a.step, a.cache_cap, a.n_splits, a.chunk);
+    const SplitDeal deal = deal_splits(a.base_len, a.batch, a.max_base, a.step, a.cache_cap, a.n_splits);
     chunk = deal.chunk;
     if (deal.n >= 0) {
       b = at / (deal.n * a.n_kv_heads);
@@ -501,19 +500,22 @@ decode_bf16_kernel(DecodeArgs a) {
 // issued before any is used; the range groups then merge in LDS.  (One wave walking the ranges
 // took 4.9 us for 8 or 32 of them: a memory round trip per 8, once for the maxima and once for
 // the sums.)  A range that saw no key (maximum -inf) adds nothing.
-template <int HD>
+template <int HD, bool kDealt>
 __global__ void __launch_bounds__(256) decode_combine_kernel(const float* __restrict__ ws_o,
                                                              const float* __restrict__ ws_ml,
                                                              const int32_t* __restrict__ base_len, int32_t batch,
                                                              int32_t n_q_heads, int32_t max_base, int32_t step,
-                                                             int32_t cache_cap, int32_t n_splits, int32_t chunk,
-                                                             int32_t row0, bf16_t* __restrict__ out) {
+                                                             int32_t cache_cap, int32_t n_splits, int32_t row0,
+                                                             bf16_t* __restrict__ out) {
   constexpr int kLanes = HD / 4, kGroups = 256 / kLanes, kBatch = 4;
   __shared__ float m_s[kGroups], l_s[kGroups];
   __shared__ __attribute__((aligned(16))) float o_s[kGroups * HD];
   const int bh = row0 + blockIdx.x, b = bh / n_q_heads, h = bh - b * n_q_heads, l = blockIdx.y;
-  const SplitPlace place = place_of(deal_splits(base_len, batch, max_base, step, cache_cap, n_splits, chunk), b);
-  if (place.n == 1) return;   // (uniform) a whole request: its output is stored
+  SplitPlace place = {n_splits, b * n_splits};
+  if constexpr (kDealt) {
+    place = place_of(deal_splits(base_len, batch, max_base, step, cache_cap, n_splits), b);
+    if (place.n == 1) return;   // (uniform) a whole request: its output is stored
+  }
   const int64_t slot0 = ((int64_t)l * batch * n_splits + place.first) * n_q_heads + (int64_t)h * place.n;
   const int grp = threadIdx.x / kLanes, d = 4 * (threadIdx.x % kLanes);
   float M = -INFINITY, den = 0.f;
@@ -561,26 +563,34 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(const float* __rest
   reinterpret_cast<uint32_t*>(out + row * HD)[threadIdx.x] = pack_bf16x2(o0 * inv, o1 * inv);
 }
 
-template <int HD>
-hipError_t launch_decode_hd(const DecodeArgs& a, dim3 grid, bool rope, bool interleaved, int32_t n_splits,
-                            const AttnShape& s, hipStream_t stream) {
+template <int HD, bool kDealt>
+hipError_t launch_decode_as(const DecodeArgs& a, dim3 grid, bool rope, bool interleaved, const AttnShape& s,
+                            hipStream_t stream) {
   if (!rope)
-    hipLaunchKernelGGL((decode_bf16_kernel<HD, false, false>), grid, dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((decode_bf16_kernel<HD, false, false, kDealt>), grid, dim3(256), 0, stream, a);
   else if (interleaved)
-    hipLaunchKernelGGL((decode_bf16_kernel<HD, true, true>), grid, dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((decode_bf16_kernel<HD, true, true, kDealt>), grid, dim3(256), 0, stream, a);
   else
-    hipLaunchKernelGGL((decode_bf16_kernel<HD, true, false>), grid, dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((decode_bf16_kernel<HD, true, false, kDealt>), grid, dim3(256), 0, stream, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || n_splits == 1) return e;
+  if (e != hipSuccess || a.n_splits == 1) return e;
   // (a grid holds fewer than 2^32 threads per dimension)
   const int64_t rows = (int64_t)s.batch * s.n_q_heads, kPart = int64_t(1) << 23;
   for (int64_t row0 = 0; row0 < rows && e == hipSuccess; row0 += kPart) {
-    hipLaunchKernelGGL(decode_combine_kernel<HD>, dim3((unsigned)std::min(rows - row0, kPart), s.n_layers), dim3(256), 0,
-                       stream, a.ws_o, a.ws_ml, a.base_len, s.batch, s.n_q_heads, a.max_base, a.step, a.cache_cap,
-                       n_splits, a.chunk, (int32_t)row0, a.out);
+    hipLaunchKernelGGL((decode_combine_kernel<HD, kDealt>), dim3((unsigned)std::min(rows - row0, kPart), s.n_layers),
+                       dim3(256), 0, stream, a.ws_o, a.ws_ml, a.base_len, s.batch, s.n_q_heads, a.max_base, a.step,
+                       a.cache_cap, a.n_splits, (int32_t)row0, a.out);
     e = hipGetLastError();
   }
   return e;
+}
+
+template <int HD>
+hipError_t launch_decode_hd(const DecodeArgs& a, dim3 grid, bool rope, bool interleaved, const AttnShape& s,
+                            hipStream_t stream) {
+  return decode_dealt(a.n_splits, a.batch, a.max_base + a.step + 1)
+             ? launch_decode_as<HD, true>(a, grid, rope, interleaved, s, stream)
+             : launch_decode_as<HD, false>(a, grid, rope, interleaved, s, stream);
 }
 
 }  // namespace
@@ -642,8 +652,8 @@ hipError_t launch_decode_bf16(const AttnShape& s, const bf16_t* q, const bf16_t*
   a.max_abs_delta = max_abs_delta;
   a.head_groups = decode_head_groups(s);
   const dim3 grid(a.head_groups * n_splits * s.batch * s.n_kv_heads, s.n_layers);
-  if (s.head_dim == 64) return launch_decode_hd<64>(a, grid, rope_table != nullptr, interleaved, n_splits, s, stream);
-  return launch_decode_hd<128>(a, grid, rope_table != nullptr, interleaved, n_splits, s, stream);
+  if (s.head_dim == 64) return launch_decode_hd<64>(a, grid, rope_table != nullptr, interleaved, s, stream);
+  return launch_decode_hd<128>(a, grid, rope_table != nullptr, interleaved, s, stream);
 }
 
 }  // namespace pic
