@@ -141,7 +141,10 @@ def _stream(stream):
     # the 6.8 us that a call of one launch spends on the host; the handle alone takes 0.2)
     if stream is None:
         import torch
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # (not a public name)
+        if raw is None:
+            return torch.cuda.current_stream().cuda_stream
+        return raw(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

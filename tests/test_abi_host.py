@@ -507,3 +507,16 @@ def test_prefill_workspace_of_launches_that_can_run_whole(lib, n_q_heads, n_kv_h
     m = _model(n_layers=1, n_q_heads=n_q_heads, n_kv_heads=n_kv_heads, head_dim=head_dim)
     need = pic.pic_prefill_workspace_bytes(m, batch, n_suffix, max_ctx)
     assert need == splits * batch * n_suffix * n_q_heads * (4 * head_dim + 8)
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    import torch
+    class Stream:
+        cuda_stream = 77
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device, raising=False)
+    assert pic._stream(None) == 103
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert pic._stream(None) == 77
+    assert pic._stream(5) == 5 and pic._stream(Stream) == 77
