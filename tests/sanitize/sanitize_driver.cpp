@@ -267,8 +267,9 @@ void fuzz_attention() {
     EXPECT(pic_suffix_prefill_attn(&m, q.p, ks.p, vs.p, ck.p, cv.p, batch, cap, ctx.as<int32_t>(), max_ctx, n_suf,
                                    0.f, out.p, ws.n ? ws.p : nullptr, ws.n, nullptr) == PIC_OK);
     EXPECT(pic::emu::launches > before);
-    // a workspace one byte short fails and launches nothing
-    if (ws.n) {
+    // a workspace one byte short fails and launches nothing (below 128 units: see optional_workspaces)
+    const int64_t units = ((int64_t)n_suf * rep + 255) / 256 * batch * Hkv * L;
+    if (ws.n && units < 128) {
       const long b2 = pic::emu::launches;
       EXPECT(pic_suffix_prefill_attn(&m, q.p, ks.p, vs.p, ck.p, cv.p, batch, cap, ctx.as<int32_t>(), max_ctx,
                                      n_suf, 0.f, out.p, ws.p, ws.n - 1, nullptr) == PIC_ERR_WORKSPACE);
@@ -350,6 +351,74 @@ void fuzz_attention() {
     EXPECT(pic_suffix_prefill_attn_rope(&m, q.p, ks.p, vs.p, ck.p, cv.p, batch, cap, ctx.as<int32_t>(), max_ctx,
                                         n_suf, table2.p, mad2, 0.f, out.p, ws.n ? ws.p : nullptr, ws.n,
                                         nullptr) == PIC_OK);
+  }
+}
+
+// ---- split decode with ranges dealt by length: long caches, garbage base lengths ----
+void fuzz_dealt_decode() {
+  for (int it = 0; it < 4; ++it) {
+    const int D = rnd(0, 1) ? 128 : 64, Hkv = (int)rnd(1, 2), rep = rnd(0, 2) ? (int)rnd(1, 8) : (int)rnd(17, 20);
+    pic_model m = model((int)rnd(1, 2), Hkv * rep, Hkv, D, PIC_BF16);
+    const int L = m.n_layers, Hq = m.n_q_heads;
+    // as many requests as are dealt, one more, or a few
+    const int32_t batch = it == 0 ? 64 : it == 1 ? 65 : (int32_t)rnd(2, 12);
+    const int32_t step = (int32_t)rnd(0, 3), dmax = (int32_t)rnd(8192, 9500), cap = dmax + step + 1;
+    const int32_t splits = it < 2 ? 8 : (int32_t)rnd(8, 40);
+    const size_t row = (size_t)D * 2, LB = (size_t)L * batch;
+    Buf q(LB * Hq * row), out(LB * Hq * row), kn(LB * Hkv * row), vn(LB * Hkv * row);
+    Buf ck(LB * Hkv * cap * row), cv(LB * Hkv * cap * row), base(batch * sizeof(int32_t));
+    Buf table(pic_rope_table_bytes(&m, dmax + step));
+    for (int form = 0; form < 3; ++form) {   // garbage, one length, one long context among empty ones
+      for (int b = 0; b < batch; ++b)
+        base.as<int32_t>()[b] = form == 0 ? garbage(dmax + 1) : form == 1 ? dmax : (b == batch / 2 ? dmax : 0);
+      Buf ws(pic_decode_workspace_bytes(&m, batch, dmax + step + 1, splits));
+      EXPECT(pic_decode_attn(&m, q.p, kn.p, vn.p, ck.p, cv.p, batch, cap, base.as<int32_t>(), step, dmax, 0.f, splits,
+                             out.p, ws.p, ws.n, nullptr) == PIC_OK);
+      EXPECT(pic_decode_attn_rope(&m, q.p, kn.p, vn.p, ck.p, cv.p, batch, cap, base.as<int32_t>(), step, dmax, table.p,
+                                  dmax + step, 0.f, splits, out.p, ws.p, ws.n, nullptr) == PIC_OK);
+    }
+  }
+}
+
+// ---- prefill split with float32 partials (128 units and more): garbage lengths and positions, every mode ----
+void fuzz_optional_prefill() {
+  for (int it = 0; it < 2; ++it) {
+    const int D = it ? 64 : 128, Hkv = 8, rep = 4;
+    pic_model m = model(1, Hkv * rep, Hkv, D, PIC_BF16);
+    const int32_t batch = it ? 16 : 8, n = it ? (int32_t)rnd(2, 40) : (int32_t)rnd(65, 90);
+    const int32_t max_ctx = (int32_t)rnd(3000, 3600), cap = max_ctx + n, mad = cap, map_cap = max_ctx + (int32_t)rnd(0, 70);
+    const int64_t pool_tokens = rnd(64, 3000);
+    const size_t row = (size_t)D * 2, toks = (size_t)batch * n;
+    Buf q(toks * Hkv * rep * row), out(toks * Hkv * rep * row), ks(toks * Hkv * row), vs(toks * Hkv * row);
+    Buf ck((size_t)batch * Hkv * cap * row), cv((size_t)batch * Hkv * cap * row), ctx(batch * sizeof(int32_t));
+    for (int b = 0; b < batch; ++b) ctx.as<int32_t>()[b] = garbage(max_ctx + 1);
+    Buf pk(Hkv * pool_tokens * row), pv(Hkv * pool_tokens * row), table(pic_rope_table_bytes(&m, mad));
+    Buf sm((size_t)batch * map_cap * 4), dm((size_t)batch * map_cap * 4), tm((size_t)batch * ((map_cap + 63) / 64) * 8);
+    for (int64_t i = 0; i < (int64_t)batch * map_cap; ++i) {
+      sm.as<int32_t>()[i] = garbage((int32_t)pool_tokens);
+      dm.as<int32_t>()[i] = garbage(mad);
+    }
+    for (size_t i = 0; i < tm.n / 8; ++i) {
+      tm.as<int32_t>()[2 * i] = garbage((int32_t)pool_tokens);
+      tm.as<int32_t>()[2 * i + 1] = garbage(mad);
+    }
+    Buf pos(toks * 4), nv(batch * 4);
+    for (size_t i = 0; i < toks; ++i) pos.as<int32_t>()[i] = garbage(cap);
+    for (int b = 0; b < batch; ++b) nv.as<int32_t>()[b] = garbage(n + 1);
+    Buf ws(pic_prefill_workspace_bytes(&m, batch, n, max_ctx));
+    EXPECT(ws.n > 0 && pic_frontier_workspace_bytes(&m, batch, n, cap) == ws.n);
+    EXPECT(pic_suffix_prefill_attn(&m, q.p, ks.p, vs.p, ck.p, cv.p, batch, cap, ctx.as<int32_t>(), max_ctx, n, 0.f, out.p,
+                                   ws.p, ws.n, nullptr) == PIC_OK);
+    EXPECT(pic_suffix_prefill_attn_rope(&m, q.p, ks.p, vs.p, ck.p, cv.p, batch, cap, ctx.as<int32_t>(), max_ctx, n, table.p,
+                                        mad, 0.f, out.p, ws.p, ws.n, nullptr) == PIC_OK);
+    for (int with_map = 0; with_map < 2; ++with_map)
+      EXPECT(pic_paged_prefill_attn(&m, pk.p, pv.p, pool_tokens, sm.as<int32_t>(), dm.as<int32_t>(), map_cap,
+                                    with_map ? tm.as<int32_t>() : nullptr, table.p, mad, q.p, ks.p, vs.p, ck.p, cv.p, batch,
+                                    cap, ctx.as<int32_t>(), max_ctx, n, 0.f, out.p, ws.p, ws.n, nullptr) == PIC_OK);
+    const long before = pic::emu::launches;
+    EXPECT(pic_frontier_prefill_attn(&m, q.p, ks.p, vs.p, ck.p, cv.p, batch, cap, pos.as<int32_t>(), nv.as<int32_t>(), n, cap,
+                                     0.f, out.p, ws.p, ws.n, nullptr) == PIC_OK);
+    EXPECT(pic::emu::launches - before == 3);   // store, attention, combine
   }
 }
 
@@ -504,6 +573,8 @@ int main(int argc, char** argv) {
     valid_compose();
     fuzz_attention();
   }
+  fuzz_dealt_decode();
+  fuzz_optional_prefill();
   if (seed == 1) {   // (no random draws)
     prefill_workspace_of_the_largest();
     decode_workspace_of_the_largest();

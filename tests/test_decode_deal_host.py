@@ -1,6 +1,7 @@
-"""How a split decode deals its key ranges to requests of uneven lengths (pic_bounds.h), on the CPU:
-the ranges fit the launch, cover every request, and the size taken is the smallest candidate that
-fits; the last candidate (the longest request in n_splits ranges) always fits."""
+"""How a split decode deals its key ranges to requests of uneven lengths (pic_bounds.h), on the CPU: the
+candidate sizes run from the mean to the longest request in n_splits ranges, which always fits; the
+size taken is the first that fits the launch, and its ranges cover every request and have workgroups
+and partial slots of their own.  (The kernels' own arithmetic is compared on the GPU.)"""
 import os
 import random
 import subprocess
@@ -56,3 +57,27 @@ def test_ranges_fit_and_cover(candidates):
         assert cs == sorted(cs) and cs[0] >= 1
         assert cs[-1] == -(-max(u) // min(s, max(u))) and ranges(cs[-1]) <= budget
         assert cs[0] * min(s, max(u)) * len(u) >= sum(u)   # (nothing smaller than the mean could fit)
+
+
+def test_size_taken_ranges_and_places(candidates):
+    rng = random.Random(1)
+    cases = []
+    for _ in range(200):
+        batch, n_splits = rng.randint(2, 64), rng.choice([8, 9, 16, 31])
+        top = rng.choice([64, 75, 300, 5000])
+        cases.append((n_splits, rng.choice([1, 3]), [rng.randint(1, top) for _ in range(batch - 1)] + [top]))
+    for (s, hq, u), cs in zip(cases, candidates([(sum(u), max(u), s, len(u)) for s, _, u in cases])):
+        fits = [sum(-(-x // c) for x in u) <= s * len(u) for c in cs]
+        size = cs[fits.index(True)]
+        assert all(not f for f in fits[:fits.index(True)]) and all(fits[fits.index(True):])   # (larger ones fit too)
+        n = [-(-x // size) for x in u]
+        first = [sum(n[:b]) for b in range(len(u))]
+        workgroups, slots = set(), set()
+        for b, x in enumerate(u):
+            assert n[b] >= 1 and (n[b] - 1) * size < x <= n[b] * size        # every range holds keys, together all
+            for h in range(hq):
+                for r in range(n[b]):
+                    workgroups.add(first[b] * hq + h * n[b] + r)             # [request][head][range], hq kv heads
+                    slots.add(first[b] * hq + h * n[b] + r)
+        assert len(slots) == len(workgroups) == sum(n) * hq
+        assert max(slots) < s * len(u) * hq
