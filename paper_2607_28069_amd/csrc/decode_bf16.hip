@@ -76,6 +76,11 @@ __device__ __forceinline__ int v_swz(int key) {
   else return (key & 3) << 1;
 }
 
+// The dealt ranges of a batch whose contexts all have the greatest length the call allows.
+struct EqualDeal {
+  int32_t units, n, chunk;   // units of every context, its ranges, keys per range
+};
+
 struct DecodeArgs {
   const bf16_t* q;        // [L][B][Hq][D]
   const bf16_t* k_new;    // [L][B][Hkv][D]
@@ -88,6 +93,7 @@ struct DecodeArgs {
   float* ws_ml;           // [L][slots][2]
   int32_t batch, cache_cap, n_q_heads, n_kv_heads, max_base, step, n_splits, chunk;
   int32_t head_groups;    // groups of up to 16 query heads per kv head (ceil(n_rep / 16))
+  EqualDeal eq;
   float scale_log2;
   const float2* table;    // rope variant: [L or 1][max_abs_delta + 1][D/2] cos/sin rows
   int64_t table_stride;
@@ -96,13 +102,17 @@ struct DecodeArgs {
 
 // How the key ranges of a split launch are dealt to the requests (pic_bounds.h): worked out by
 // every wave from the context lengths, request b in lane b.  Request b's partials are slots
-// [Hq first, Hq (first + n)), query head by query head.  Contexts of one length take a short way
-// to the same ranges (the long one costs about 0.5 us, paid in the kernel and its combine).
+// [Hq first, Hq (first + n)), query head by query head.  Contexts of one length take a short way to
+// the same ranges (the long one costs about 0.5 us, paid in the kernel and its combine), and where that
+// is the greatest length the host has worked them out (EqualDeal): the place follows, and the combine
+// loads its partials, while the lengths are on their way.
 struct SplitDeal {
   int32_t chunk;   // keys per range, a multiple of 128
   int32_t n;       // ranges of every request; -1: lane b holds those of request b in mine
   int32_t mine;
-  int32_t base;    // dealt: lane b holds the context length of request b
+};
+struct SplitLens {
+  int32_t u, base;   // lane b: request b's units and context length
 };
 struct SplitPlace {
   int32_t n, first;   // ranges of the request; those of the requests before it
@@ -113,18 +123,25 @@ __device__ __forceinline__ int32_t ceil_div24(int32_t u, int32_t c, float inv) {
   const int32_t r = u - q * c;
   return q + (r > 0 ? 1 : 0) + (r > c ? 1 : 0) - (r <= -c ? 1 : 0);
 }
-__device__ __forceinline__ SplitDeal deal_splits(const int32_t* base_len, int32_t batch, int32_t max_base, int32_t step,
-                                                 int32_t cache_cap, int32_t n_splits) {
+__device__ __forceinline__ SplitLens split_lens(const int32_t* base_len, int32_t batch, int32_t max_base, int32_t step,
+                                                int32_t cache_cap) {
   const int lane = threadIdx.x & 63;
-  int32_t u = 0, base = 0;
+  SplitLens x = {0, 0};
   if (lane < batch) {
-    base = clamp_len(base_len[lane], max_base);
-    u = decode_units(min(base + step + 1, cache_cap));
+    x.base = clamp_len(base_len[lane], max_base);
+    x.u = decode_units(min(x.base + step + 1, cache_cap));
   }
-  const int32_t u0 = __builtin_amdgcn_readfirstlane(u);
-  if (__ballot(lane < batch && u != u0) == 0) {
+  return x;
+}
+__device__ __forceinline__ bool all_of(const SplitLens& x, int32_t units, int32_t batch) {
+  return __ballot((int)(threadIdx.x & 63) < batch && x.u != units) == 0;
+}
+__device__ __forceinline__ SplitDeal deal_splits(const SplitLens& x, int32_t batch, int32_t n_splits) {
+  const int lane = threadIdx.x & 63;
+  const int32_t u = x.u, u0 = __builtin_amdgcn_readfirstlane(u);
+  if (all_of(x, u0, batch)) {
     const int32_t s = min(n_splits, u0), cu = __builtin_amdgcn_readfirstlane(ceil_div24(u0, s, __builtin_amdgcn_rcpf((float)s)));
-    return {cu * kDecodeUnit, __builtin_amdgcn_readfirstlane(ceil_div24(u0, cu, __builtin_amdgcn_rcpf((float)cu))), 0, base};
+    return {cu * kDecodeUnit, __builtin_amdgcn_readfirstlane(ceil_div24(u0, cu, __builtin_amdgcn_rcpf((float)cu))), 0};
   }
   int32_t total = 0, longest = 0;
   for (int b = 0; b < batch; ++b) {
@@ -139,7 +156,7 @@ __device__ __forceinline__ SplitDeal deal_splits(const int32_t* base_len, int32_
   for (int b = 0; b < batch; ++b) sum += ceil_div24(__builtin_amdgcn_readlane(u, b), c, inv);
   const uint64_t fits = __ballot(sum <= n_splits * batch);   // (lane 63: always)
   const int32_t cu = __builtin_amdgcn_readlane(c, __ffsll((unsigned long long)fits) - 1);
-  return {cu * kDecodeUnit, -1, ceil_div24(u, cu, __builtin_amdgcn_rcpf((float)cu)), base};
+  return {cu * kDecodeUnit, -1, ceil_div24(u, cu, __builtin_amdgcn_rcpf((float)cu))};
 }
 __device__ __forceinline__ SplitPlace place_of(const SplitDeal& d, int b) {   // b uniform
   if (d.n >= 0) return {d.n, b * d.n};
@@ -226,24 +243,33 @@ decode_bf16_kernel(DecodeArgs a) {
     place = {a.n_splits, b * a.n_splits};
     base = clamp_len(a.base_len[b], a.max_base);
   } else {
-    const SplitDeal deal = deal_splits(a.base_len, a.batch, a.max_base, a.step, a.cache_cap, a.n_splits);
-    chunk = deal.chunk;
-    if (deal.n >= 0) {
-      b = at / (deal.n * a.n_kv_heads);
-      place = place_of(deal, b);
-    } else {
-      place = {0, 0};
-      for (b = 0; b < a.batch; ++b) {
-        place.n = __builtin_amdgcn_readlane(deal.mine, b);
-        if (at < (place.first + place.n) * a.n_kv_heads) break;
-        place.first += place.n;
+    const SplitLens lens = split_lens(a.base_len, a.batch, a.max_base, a.step, a.cache_cap);
+    const int bg = at / a.eq.n;
+    split = at % a.eq.n;
+    b = bg / a.n_kv_heads;
+    g = bg % a.n_kv_heads;
+    place = {a.eq.n, b * a.eq.n};
+    chunk = a.eq.chunk;
+    if (!all_of(lens, a.eq.units, a.batch)) {
+      const SplitDeal deal = deal_splits(lens, a.batch, a.n_splits);
+      chunk = deal.chunk;
+      if (deal.n >= 0) {
+        b = at / (deal.n * a.n_kv_heads);
+        place = place_of(deal, b);
+      } else {
+        place = {0, 0};
+        for (b = 0; b < a.batch; ++b) {
+          place.n = __builtin_amdgcn_readlane(deal.mine, b);
+          if (at < (place.first + place.n) * a.n_kv_heads) break;
+          place.first += place.n;
+        }
       }
+      const int in_b = at - place.first * a.n_kv_heads;
+      g = in_b / place.n;
+      split = in_b - g * place.n;
     }
     if (b >= a.batch) return;   // (uniform) more workgroups than ranges
-    const int in_b = at - place.first * a.n_kv_heads;
-    g = in_b / place.n;
-    split = in_b - g * place.n;
-    base = __builtin_amdgcn_readlane(deal.base, b);
+    base = __builtin_amdgcn_readlane(lens.base, b);
   }
   const int l = blockIdx.y;
   const int n_rep = a.n_q_heads / a.n_kv_heads;
@@ -505,30 +531,42 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(const float* __rest
                                                              const float* __restrict__ ws_ml,
                                                              const int32_t* __restrict__ base_len, int32_t batch,
                                                              int32_t n_q_heads, int32_t max_base, int32_t step,
-                                                             int32_t cache_cap, int32_t n_splits, int32_t row0,
-                                                             bf16_t* __restrict__ out) {
+                                                             int32_t cache_cap, int32_t n_splits, EqualDeal eq,
+                                                             int32_t row0, bf16_t* __restrict__ out) {
   constexpr int kLanes = HD / 4, kGroups = 256 / kLanes, kBatch = 4;
   __shared__ float m_s[kGroups], l_s[kGroups];
   __shared__ __attribute__((aligned(16))) float o_s[kGroups * HD];
   const int bh = row0 + blockIdx.x, b = bh / n_q_heads, h = bh - b * n_q_heads, l = blockIdx.y;
-  SplitPlace place = {n_splits, b * n_splits};
-  if constexpr (kDealt) {
-    place = place_of(deal_splits(base_len, batch, max_base, step, cache_cap, n_splits), b);
-    if (place.n == 1) return;   // (uniform) a whole request: its output is stored
-  }
-  const int64_t slot0 = ((int64_t)l * batch * n_splits + place.first) * n_q_heads + (int64_t)h * place.n;
   const int grp = threadIdx.x / kLanes, d = 4 * (threadIdx.x % kLanes);
-  float M = -INFINITY, den = 0.f;
-  f32x4_t o = {};
-  for (int s0 = grp; s0 < place.n; s0 += kBatch * kGroups) {
-    float2 ml[kBatch];
-    f32x4_t x[kBatch];
+  const int64_t layer0 = (int64_t)l * batch * n_splits * n_q_heads;   // (slots)
+  const int32_t n0 = kDealt ? eq.n : n_splits;
+  SplitPlace place = {n0, b * n0};
+  float2 ml[kBatch];
+  f32x4_t x[kBatch];
+  auto load = [&](int s0) {
+    const int64_t slot0 = layer0 + (int64_t)place.first * n_q_heads + (int64_t)h * place.n;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const int s = s0 + u * kGroups;
       ml[u] = s < place.n ? *reinterpret_cast<const float2*>(ws_ml + 2 * (slot0 + s)) : make_float2(-INFINITY, 0.f);
       x[u] = s < place.n ? *reinterpret_cast<const f32x4_t*>(ws_o + (slot0 + s) * HD + d) : f32x4_t{};
     }
+  };
+  if constexpr (kDealt) {
+    const SplitLens lens = split_lens(base_len, batch, max_base, step, cache_cap);
+    load(grp);   // (equal ranges fit the array whatever the lengths are)
+    if (!all_of(lens, eq.units, batch)) {
+      place = place_of(deal_splits(lens, batch, n_splits), b);
+      load(grp);
+    }
+    if (place.n == 1) return;   // (uniform) a whole request: its output is stored
+  } else {
+    load(grp);
+  }
+  float M = -INFINITY, den = 0.f;
+  f32x4_t o = {};
+  for (int s0 = grp; s0 < place.n; s0 += kBatch * kGroups) {
+    if (s0 != grp) load(s0);
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       if (ml[u].x == -INFINITY) continue;
@@ -579,7 +617,7 @@ hipError_t launch_decode_as(const DecodeArgs& a, dim3 grid, bool rope, bool inte
   for (int64_t row0 = 0; row0 < rows && e == hipSuccess; row0 += kPart) {
     hipLaunchKernelGGL((decode_combine_kernel<HD, kDealt>), dim3((unsigned)std::min(rows - row0, kPart), s.n_layers),
                        dim3(256), 0, stream, a.ws_o, a.ws_ml, a.base_len, s.batch, s.n_q_heads, a.max_base, a.step,
-                       a.cache_cap, a.n_splits, (int32_t)row0, a.out);
+                       a.cache_cap, a.n_splits, a.eq, (int32_t)row0, a.out);
     e = hipGetLastError();
   }
   return e;
@@ -646,6 +684,13 @@ hipError_t launch_decode_bf16(const AttnShape& s, const bf16_t* q, const bf16_t*
   a.n_splits = n_splits;
   const int32_t chunk = ceil_div(max_len, n_splits);
   a.chunk = (int32_t)min((int64_t)decode_units(chunk) * kDecodeUnit, (int64_t)INT32_MAX / kDecodeUnit * kDecodeUnit);
+  a.eq = {};
+  if (decode_dealt(n_splits, s.batch, max_len)) {
+    a.eq.units = decode_units(std::min(max_len, s.cache_cap));
+    const int32_t per = ceil_div(a.eq.units, std::min(n_splits, a.eq.units));   // units per range
+    a.eq.n = ceil_div(a.eq.units, per);
+    a.eq.chunk = per * kDecodeUnit;
+  }
   a.scale_log2 = s.scale_log2;
   a.table = rope_table;
   a.table_stride = table_stride;

@@ -99,3 +99,18 @@ def test_noalloc_full_launch_equals_the_call_without_a_workspace():
         _check(x, base, 0)
         outs.append(x["out"])
     assert torch.equal(outs[0], outs[1])
+
+
+# lengths against the greatest the call allows, whose equal ranges the host works out: all at it, all
+# one unit or far below it, one below it, garbage above it (clamped)
+@pytest.mark.parametrize("base,max_base", [([9000] * 3, 9000), ([9000] * 3, 9500), ([8300] * 3, 20000), ([9000, 9000, 8871], 9000),
+                                           ([9000, 8999, 9000], 9000), ([30000, 12000, 9000], 9000)])
+@pytest.mark.parametrize("d,n_splits", [(128, 8), (64, 40)])
+def test_lengths_and_the_greatest_allowed(base, max_base, d, n_splits):
+    x = _inputs(8, 2, d, [max_base] * len(base), 1)
+    x["base"] = torch.tensor(base, dtype=torch.int32, device=DEV)
+    ws = torch.full((pic.pic_decode_workspace_bytes(x["model"], 3, max_base + 2, n_splits) // 4,), float("nan"), device=DEV)
+    pic.pic_decode_attn(x["model"], x["q"], x["k"], x["v"], x["K"], x["V"], 3, x["cap"], x["base"], 1, max_base, x["out"], ws,
+                        n_splits=n_splits)
+    torch.cuda.synchronize()
+    _check(x, [min(b, max_base) for b in base], 1)
