@@ -1146,10 +1146,11 @@ prefill_bf16_kernel(PrefillArgs a) {
   // its 33 us launch.
   const float inv = 1.f / l_tot;
   // (inline layouts of few rows, which write little, store from the registers all the same: through
-  // LDS 20 rows of 39 requests took 18.0 us instead of 17.1, 28 of 4 13.1 and 12.5; 256 of 16 56.4 and 58.2)
-  if (kTable && a.n_splits == 1 && M <= 64) {
+  // LDS 20 rows of 39 requests took 18.0 us instead of 17.1, 28 of 4 13.1 and 12.5, 35 of one request in
+  // splits 18.3 and 17.7; 256 of 16 56.4 and 58.2)
+  if (kTable && M <= 64 && (a.n_splits == 1 || !a.f32_partials)) {
     if (!row_ok) return;
-    bf16_t* op = a.out + row_at(r, tok) * kHD;
+    bf16_t* op = (a.n_splits == 1 ? a.out : static_cast<bf16_t*>(a.ws_o) + split * a.rows_total * kHD) + row_at(r, tok) * kHD;
 #pragma unroll
     for (int db = 0; db < kDB; ++db)
 #pragma unroll
