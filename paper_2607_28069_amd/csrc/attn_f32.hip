@@ -22,7 +22,7 @@
 //    library product reaches 150 TFLOP/s): a 16-key tile of 16 rows at head_dim 64 is 32 products
 //    of 32 cycles for 8 KB loaded.  Measured against a kernel with one row per workgroup and
 //    plain vector arithmetic: 16 heads over 4 kv heads at head_dim 64, four requests of 2077 keys,
-//    61 tokens 384 -> 26.3 us; four requests of 4160 keys, 32 heads over 8 at head_dim 128, 64
+//    61 tokens 356 -> 26.0 us; four requests of 4160 keys, 32 heads over 8 at head_dim 128, 64
 //    tokens 3520 -> 148 us (119 TFLOP/s); a decode step of one request at 4096 keys 293 -> 41 us.
 //  * New tokens' K/V are read from k_new / v_new and stored into the cache by the workgroups of
 //    their (request, kv head), each a share of the rows; no workgroup reads those slots from the

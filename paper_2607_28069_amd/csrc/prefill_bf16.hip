@@ -29,7 +29,7 @@
 //    hand (scheduling barriers): each LDS operand is read one product ahead of its use, and
 //    the PV products of a tile's last slice are issued after the tile barrier, covering the
 //    latency of the next tile's first reads.
-//  * Head dim D = 128 in every mode, or 64 in the suffix and table modes.  At 64 a row is 8
+//  * Head dim D = 128 or 64, in every mode.  At 64 a row is 8
 //    chunks, one load instruction moves 8 rows, the score chains take 4 k steps and the output
 //    2 blocks of 32 dims; the tile body keeps its order, with one score product per two pairs
 //    of probabilities (the exponentials per flop double, so the vector unit limits it sooner).
@@ -63,7 +63,7 @@ constexpr int kRowsPerWave = 32;
 constexpr int kRowsPerWG = kWaves * kRowsPerWave;
 constexpr int kKeys = 64;                      // keys per tile
 constexpr int kNumXcd = 8;
-// Sizes that follow the head dim D (128; or 64 in the suffix and table modes).  A row is D / 8
+// Sizes that follow the head dim D (128 or 64).  A row is D / 8
 // 16-byte chunks, and one 1 KB load instruction of a wave moves 64 / (D / 8) rows of a tile.
 template <int HD>
 struct Dims {
@@ -1141,9 +1141,9 @@ prefill_bf16_kernel(PrefillArgs a) {
   // Normalised: the output in bf16, or one split's share of it in bf16 or float32 (with its
   // reference max and row sum, the weights the combine needs).  A lane holds 8 bytes here and there
   // of one row, so the wave's 32 rows go through LDS (the tiles' buffers, free since the last
-  // barrier) and leave as whole rows, 16 bytes per lane.  Stored from the registers, 16 bytes of
-  // 32 rows per instruction, the partials of a lone request (15 splits x 4096 rows) took 9 us of
-  // its 33 us launch.
+  // barrier) and leave as whole rows, 16 bytes per lane.  Against stores from the registers, 16
+  // bytes of 32 rows per instruction, a lone request's launch (15 splits x 4096 rows of partials)
+  // took 30.5 us instead of 33.3.
   const float inv = 1.f / l_tot;
   // (inline layouts of few rows, which write little, store from the registers all the same: through
   // LDS 20 rows of 39 requests took 18.0 us instead of 17.1, 28 of 4 13.1 and 12.5, 35 of one request in
@@ -1216,7 +1216,7 @@ prefill_bf16_kernel(PrefillArgs a) {
 }
 
 // Merge the key-range splits of each query row by log-sum-exp.  Split s left its output
-// normalised by its own row sum l_s (bf16) with its reference max m_s: the row is
+// normalised by its own row sum l_s (PT: bf16 or float32) with its reference max m_s: the row is
 // sum_s w_s O_s / sum_s w_s with w_s = 2^(m_s - M) l_s, M any common reference.  grid (rows_total / 16),
 // 2 D threads: D / 8 lanes per row, 8 head dims per lane; every split's loads are issued without a branch
 // between them (a split that saw no key of the row, reference max -inf, is dropped by a

@@ -230,7 +230,7 @@ def test_argument_checks_fail_before_any_launch(lib):
     assert _prefill(lib, m, q=MIS) == -5
     assert _prefill(lib, m, ctx=None) == -1
     assert _prefill(lib, m, scale=-1.0) == -1
-    assert _prefill(lib, _model(head_dim=64)) != -2      # bf16 at head_dim 64: the row-wise kernel
+    assert _prefill(lib, _model(head_dim=64)) != -2      # bf16 at head_dim 64
     assert _prefill(lib, m, ns=0) == 0
 
     assert _frontier(lib, m, max_len=601) == -4          # longer than the cache

@@ -1,8 +1,7 @@
 """A softmax scale other than the default 1/sqrt(head_dim), through every attention entry point
 that takes one, against the oracle with the same scale: the matrix-core suffix prefill (split
 over key ranges, and unsplit), the zero-copy prefill (per key and with the tile map), the frontier
-prefill, split and unsplit decode, and the row path (float32 at head_dim 64, bf16 at head_dim
-64).  A scale of 0.05 sits well away from the default (0.088 at head_dim 128, 0.125 at 64), so a
+prefill, split and unsplit decode, and float32 and bf16 at head_dim 64.  A scale of 0.05 sits well away from the default (0.088 at head_dim 128, 0.125 at 64), so a
 call that ignored it would fail the attention tolerance."""
 import dataclasses
 
