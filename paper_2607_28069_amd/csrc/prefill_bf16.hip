@@ -1504,13 +1504,17 @@ hipError_t launch(const AttnShape& s, PrefillArgs a, int mode, bool interleaved,
   //   2 m-tiles   48: 1.09 / 1.00    62: 1.05 / 0.96, last 32 1.02 / 1.01   96: 1.03 / 0.96, 1.02 / 1.01
   //   3           48: 1.23 / 1.00    78: 1.08 / 0.98, last 32 1.08 / 1.02   96: 1.05 / 0.95, 1.10 / 1.02
   //   4           60: 1.15 / 1.01    80: 1.24 / 1.01, last 64 1.24 / 1.01   96: 1.12 / 0.98, 1.10 / 1.00
-  //   8           48: 1.24 / 1.04    80: 1.20 / 1.03, last 64 1.22 / 1.03  144: last 64 1.06 / 1.01
+  //   8           48: 1.24 / 1.04    80: 1.20 / 1.03, last 64 1.22 / 1.03  144: last 32 1.06 / 1.01
+  // (past 96 the last 32 whatever the m-tiles: 9 m-tiles of 576 inline tokens, 144 per XCD, 848 us, 870
+  // with the last 64)
   // (pairs that the XCDs do not share evenly keep the plain order: an XCD's range then starts and ends
   // inside a pair)
   const int32_t pairs = s.batch * s.n_kv_heads;
   if (mode == kModeTable && p.n_splits == 1 && p.m_tiles > 1 && pairs % kNumXcd == 0) {
-    const int32_t per_xcd = pairs / kNumXcd, last = p.m_tiles < 4 ? 32 : 64;
-    a.tail_bgs = (int64_t)per_xcd * p.m_tiles <= last + 16 ? per_xcd : std::min(per_xcd, (last + p.m_tiles - 1) / p.m_tiles);
+    const int32_t per_xcd = pairs / kNumXcd;
+    const int64_t wgs = (int64_t)per_xcd * p.m_tiles;
+    const int32_t last = p.m_tiles < 4 || wgs > 96 ? 32 : 64;
+    a.tail_bgs = wgs <= (p.m_tiles < 4 ? 48 : 80) ? per_xcd : std::min(per_xcd, (last + p.m_tiles - 1) / p.m_tiles);
   }
   a.rows_total = (int64_t)s.n_layers * s.batch * n_q * s.n_q_heads;
   a.ws_o = workspace;
