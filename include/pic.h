@@ -240,7 +240,9 @@ pic_status pic_compose_shared(const pic_model* model, const void* pool_k, const 
                               not 16-byte aligned, run in one key range.  Above 192 units the
                               query says 0; below, it is a few float32 (under 128 units bfloat16)
                               outputs per query row and head: 8 requests x 128 tokens, 32 heads of
-                              128: 34 MB; at most some 100 MB at 32K keys, 150 MB at 128K.
+                              128: 34 MB; at most some 100 MB at 32K keys, 150 MB at 128K.  A
+                              workspace of that size is written: calls that may overlap on the
+                              GPU bring one each.
    The prefill kernels (this call and 3a-3c) address one cache stream [cache_cap][D], one
    request's suffix rows [n_suffix][Hkv][D] and one pool head [pool_tokens][D] with 32-bit byte
    offsets: each of cache_cap, n_suffix * Hkv and pool_tokens must be below 2^24
