@@ -65,9 +65,11 @@ int prefill_bf16_splits_held(const AttnShape& s, int32_t n_suffix, int32_t max_c
 //    76 / 61, 10 of 10K x 128 (160 units) 245 / 227, 12 of 32K x 128 (192) 828 / 772; contexts down to
 //    half as long: 225 / 160, 64 / 50, 230 / 209.
 //  * Beyond, none: up to 256 there is little to gain (28 requests of 32K x 32 tokens, 224 units: 701 us
-//    whole, 772 in 8), and past a full round, where equal contexts would gain, rounds are not in lockstep:
-//    uneven contexts fill the last one by themselves (40 requests of 2K to 4K keys, 28/4 heads x 73
-//    tokens, 320 units: 165 us whole, 196 in 2; 48 of 5K to 10K x 32 tokens, 384 units: 345 / 379).
+//    whole, 772 in 8), and past a full round, where long equal contexts would gain (264 units over 32K
+//    1.2 to 1.4 times), rounds are not in lockstep: uneven contexts fill the last one by themselves (40
+//    requests of 2K to 4K keys, 28/4 heads x 73 tokens, 320 units: 165 us whole, 196 in 2; 48 of 5K to
+//    10K x 32 tokens, 384 units: 345 / 379), and inline layouts, which plan alike, by their dispatch
+//    order (10 of 16K x 252 inline tokens, 320 units: 439 / 591).
 SplitPlan plan_prefill_splits(const AttnShape& s, int32_t n_suffix, int32_t max_ctx, size_t ws_bytes) {
   SplitPlan p;
   const int held = prefill_bf16_splits_held(s, n_suffix, max_ctx);
